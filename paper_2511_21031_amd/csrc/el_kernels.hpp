@@ -316,9 +316,10 @@ __device__ inline void el_face_flux(const double (&st)[6][5], const Phys &ph, do
                                     double &uL, double &uR)
 {
     double WL[5], WR[5];
+#pragma unroll
     for (int v = 0; v < 5; ++v) {
-        WL[v] = weno5(st[0][v], st[1][v], st[2][v], st[3][v], st[4][v]);
-        WR[v] = weno5(st[5][v], st[4][v], st[3][v], st[2][v], st[1][v]);
+        const double s[6] = {st[0][v], st[1][v], st[2][v], st[3][v], st[4][v], st[5][v]};
+        weno5_pair(s, WL[v], WR[v]);
     }
     if (!(WL[0] > 0.0 && WR[0] > 0.0 && WL[4] + ph.pi_inf > 0.0 && WR[4] + ph.pi_inf > 0.0)) {
         for (int v = 0; v < 5; ++v) {

@@ -228,8 +228,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs &A, const Grid &g, co
 #pragma unroll
                     for (int o = 0; o < 6; ++o) s[o] = fl6[o] ? -s[o] : s[o];
                 }
-                WL[v] = weno5(s[0], s[1], s[2], s[3], s[4]);
-                WR[v] = weno5(s[5], s[4], s[3], s[2], s[1]);
+                weno5_pair(s, WL[v], WR[v]);
                 WcL[v] = s[2];
                 WcR[v] = s[3];
             }
