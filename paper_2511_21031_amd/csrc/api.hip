@@ -950,8 +950,8 @@ int el_bubbles(bub_ctx *c, const ElGrid &g, const double *P, double *b, long lon
     O.rtol = c->opts.sub_rtol > 0.0 ? c->opts.sub_rtol : 1e-4;
     O.max_substeps = c->opts.max_substeps > 0 ? c->opts.max_substeps : 10000;
     O.nsub = nsub;
-    if (pw_fast(c)) hipLaunchKernelGGL(k_el_ode<true>, dim3(blocks_for(nb)), dim3(256), 0, s, O, c->ph, c->d_sc);
-    else hipLaunchKernelGGL(k_el_ode<false>, dim3(blocks_for(nb)), dim3(256), 0, s, O, c->ph, c->d_sc);
+    if (pw_fast(c)) hipLaunchKernelGGL(k_el_ode<PW_FIFTHS>, dim3(blocks_for(nb)), dim3(256), 0, s, O, c->ph, c->d_sc);
+    else hipLaunchKernelGGL(k_el_ode<PW_GENERAL>, dim3(blocks_for(nb)), dim3(256), 0, s, O, c->ph, c->d_sc);
     prof_end(c, pr, s);
     return hipGetLastError() == hipSuccess ? BUB_OK : BUB_EHIP;
 }

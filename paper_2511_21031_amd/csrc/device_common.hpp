@@ -19,9 +19,14 @@ constexpr double FOUR_PI_3 = 4.18879020478639098461685784437;  // 4 pi / 3
 constexpr double FOUR_PI = 12.5663706143591729538505735331;    // 4 pi
 
 // Bubble contents of a context, compiled into the kernels that need them: polytropic gas with the
-// general power, polytropic gas with the fifth-root power (3 kappa a whole number of fifths), or gas and
-// vapour with heat and vapour transfer at the wall (four state fields per bin instead of two).
-enum Contents : int { CT_POLY = 0, CT_FIFTHS = 1, CT_TRANSFER = 2 };
+// general power, polytropic gas with the fifth-root power (3 kappa a whole number of fifths), gas and
+// vapour with heat and vapour transfer at the wall (four state fields per bin instead of two), or
+// polytropic air (3 kappa = 21/5, the fifth-root power without a branch).
+enum Contents : int { CT_POLY = 0, CT_FIFTHS = 1, CT_TRANSFER = 2, CT_AIR = 3 };
+
+// Form of the polytropic power of a kernel (kpow): general, fifth-root, fifth-root for 21/5.
+enum PowerForm : int { PW_GENERAL = 0, PW_FIFTHS = 1, PW_AIR = 2 };
+__host__ __device__ constexpr int pw_of(int ct) { return ct == CT_AIR ? PW_AIR : ct == CT_FIFTHS ? PW_FIFTHS : PW_GENERAL; }
 
 // Physical constants, passed by value (kernel argument segment -> SGPRs).
 struct Phys {
@@ -206,23 +211,32 @@ __device__ inline double ppow(double x, double p, const double *__restrict__ C)
 }
 
 // x^p for p = (5c - d)/5, c >= 1 and 0 <= d <= 4 (the polytropic power 3 kappa of kappa = 1, 1.4, 5/3,
-// ...), as x^c z^d with z = x^(-1/5): Newton's iteration on x z^5 = 1, z <- z (6 - x z^5) / 5, converges
-// quadratically without a division; it starts from the FP32 hardware log2 / exp2 estimate (relative error
-// below 2e-6 for x in [1e-30, 1e30]) and takes two steps (below 1e-20 before rounding).  Measured against
-// an 80-bit reference: at most 14 ulp for p = 4.2 over x in [e^-8, e^8], the error of z^4 (the general
-// power is within 1.2 ulp, at about three times the instructions).  x must lie in [1e-30, 1e30].
-__device__ __forceinline__ double pow_fifths(double x, int c, int d)
+// ...), as x^c z^d with z = x^(-1/5).  z starts from the FP32 hardware log2 / exp2 estimate (relative error
+// e below 2e-6 for x in [1e-30, 1e30]) and takes one step of the third-order iteration below, which leaves
+// 11 e^3 (below 1e-16) and ends in one rounding; two Newton steps took five operations more and rounded
+// twice.  Against an 80-bit reference over x in
+// [e^-8, e^8], p = 4.2: at most 5.3 ulp, 1.2 rms (two Newton steps: 8.1 and 2.0; the general power is within
+// 1.2 ulp at about four times the instructions).  x must lie in [1e-30, 1e30].
+__device__ __forceinline__ double fifth_root_inv(double x)
 {
     double z = (double)__builtin_amdgcn_exp2f(-0.2f * __builtin_amdgcn_logf((float)x));
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const double z2 = z * z, z4 = z2 * z2;
-        z = (z * 0.2) * fma(-x, z4 * z, 6.0);
-    }
-    if (c == 5 && d == 4) {   // air, 3 kappa = 21/5: straight-line powers (the branch is uniform)
-        const double x2 = x * x, z2 = z * z;
-        return ((x2 * x2) * x) * (z2 * z2);
-    }
+    const double z2 = z * z;
+    const double h = fma(x, (z2 * z2) * z, -1.0);   // z = x^(-1/5) (1 + h)^(1/5)
+    return fma(z * h, fma(h, 0.12, -0.2), z);       // (1 + h)^(-1/5) = 1 - h/5 + 3 h^2/25 - ...
+}
+
+// Air, 3 kappa = 21/5: straight-line powers.
+__device__ __forceinline__ double pow_air(double x)
+{
+    const double z = fifth_root_inv(x);
+    const double x2 = x * x, z2 = z * z;
+    return ((x2 * x2) * x) * (z2 * z2);
+}
+
+__device__ __forceinline__ double pow_fifths(double x, int c, int d)
+{
+    if (c == 5 && d == 4) return pow_air(x);   // (the branch is uniform)
+    const double z = fifth_root_inv(x);
     double xc = 1.0, b = x;
     for (int e = c; e; e >>= 1) {
         if (e & 1) xc *= b;
@@ -239,10 +253,11 @@ __device__ __forceinline__ double pow_fifths(double x, int c, int d)
 // exp2(p log2 x).  The form is a template parameter of the kernels, not a branch: a branch kept both
 // forms' registers live through the callers' bin loops (the 2D stage kernel went from 128 to 162 VGPRs
 // and lost a wave per SIMD).
-template <bool PW>
+template <int PW>
 __device__ __forceinline__ double kpow(double x, const Phys &ph, const double *__restrict__ C)
 {
-    if constexpr (PW) return pow_fifths(x, ph.pw_c, ph.pw_d);
+    if constexpr (PW == PW_AIR) return pow_air(x);
+    else if constexpr (PW == PW_FIFTHS) return pow_fifths(x, ph.pw_c, ph.pw_d);
     else return C ? ppow(x, ph.kappa3, C) : exp2(ph.kappa3 * log2(x));
 }
 
@@ -345,37 +360,39 @@ __device__ inline float tsqrt(float x) { return __builtin_sqrtf(x); }
 __device__ inline double tdiv(double a, double b) { return a / b; }
 __device__ inline float tdiv(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
 
-// Keller--Miksis wall acceleration (eq. keller_miksis) with polytropic
-// contents; the R-ddot part of d(p_bw)/dt that comes from the viscous term is
-// moved to the left-hand side (exact rearrangement).
-// irho = 1/rho and ic = 1/c of the driving liquid are passed in (shared by all bins of a cell).
-template <bool PW>
-__device__ inline double km_rddot(const Phys &ph, double R, double V, double r0, double pg0,
-                                  double pinf, double irho, double ic)
+// Keller--Miksis wall acceleration (eq. keller_miksis) for contents of pressure pb; the R-ddot part of
+// d(p_bw)/dt that comes from the viscous term is moved to the left-hand side (exact rearrangement).
+// t = (4 mu V + 2 sigma)/R, so p_bw = pb - t; rd = R times the rest of d(p_bw)/dt (the 1/R of that
+// derivative cancels: R d(p_bw)/dt = R dp_b/dt + V t).  irho = 1/rho and ic = 1/c of the driving liquid are
+// passed in (shared by all bins of a cell).  Its operations are fixed (no contraction), so every kernel that
+// takes it gives the same bits; with the 1/R cancelled it is ten operations shorter than the plain form.
+__device__ __forceinline__ double km_accel(const Phys &ph, double R, double V, double pb, double rd, double t,
+                                           double pinf, double irho, double ic)
 {
-    double iR = frcp(R);
-    double pb = pg0 * kpow<PW>(r0 * iR, ph, nullptr);
-    double pbw = pb - ph.mu4 * V * iR - ph.sigma2 * iR;
-    double dpbw = (-ph.kappa3 * pb * V + ph.mu4 * V * V * iR + ph.sigma2 * V * iR) * iR;
-    double irc = irho * ic;
-    double num = (1.0 + V * ic) * (pbw - pinf) * irho + R * dpbw * irc - 1.5 * V * V * (1.0 - V * ic * (1.0 / 3.0));
-    double den = R * (1.0 - V * ic) + ph.mu4 * irc;
+#pragma clang fp contract(off)
+    const double irc = irho * ic, vi = V * ic;
+    const double num = fma((1.0 + vi) * ((pb - t) - pinf), irho, fma(rd, irc, -(V * V) * fma(-0.5, vi, 1.5)));
+    const double den = fma(R, 1.0 - vi, ph.mu4 * irc);
     return num * frcp(den);
 }
 
-// The same with the general form of the power from ppow (table C in LDS).
-template <bool PW>
-__device__ inline double km_rddot_t(const Phys &ph, double R, double V, double r0, double pg0,
-                                    double pinf, double irho, double ic, const double *__restrict__ C)
+// Polytropic contents.  C: the table of the general power (in LDS, or null for the library's).
+template <int PW>
+__device__ __forceinline__ double km_rddot_t(const Phys &ph, double R, double V, double r0, double pg0, double pinf,
+                                             double irho, double ic, const double *__restrict__ C)
 {
-    double iR = frcp(R);
-    double pb = pg0 * kpow<PW>(r0 * iR, ph, C);
-    double pbw = pb - ph.mu4 * V * iR - ph.sigma2 * iR;
-    double dpbw = (-ph.kappa3 * pb * V + ph.mu4 * V * V * iR + ph.sigma2 * V * iR) * iR;
-    double irc = irho * ic;
-    double num = (1.0 + V * ic) * (pbw - pinf) * irho + R * dpbw * irc - 1.5 * V * V * (1.0 - V * ic * (1.0 / 3.0));
-    double den = R * (1.0 - V * ic) + ph.mu4 * irc;
-    return num * frcp(den);
+#pragma clang fp contract(off)
+    const double iR = frcp(R);
+    const double pb = pg0 * kpow<PW>(r0 * iR, ph, C);
+    const double t = fma(ph.mu4, V, ph.sigma2) * iR;
+    return km_accel(ph, R, V, pb, V * fma(-ph.kappa3, pb, t), t, pinf, irho, ic);
+}
+
+template <int PW>
+__device__ __forceinline__ double km_rddot(const Phys &ph, double R, double V, double r0, double pg0, double pinf,
+                                           double irho, double ic)
+{
+    return km_rddot_t<PW>(ph, R, V, r0, pg0, pinf, irho, ic, nullptr);
 }
 
 // Transfer contents of one bubble (Sec. 2, eq. massVaporRate and the contents-pressure equation): the
@@ -388,30 +405,26 @@ __device__ inline double km_rddot_t(const Phys &ph, double R, double V, double r
 __device__ inline void contents_rates(const Phys &ph, double R, double V, double p, double m, double mg,
                                       double &pdot, double &mdot)
 {
+#pragma clang fp contract(off)
     const double iR = frcp(R);
-    const double Tbar = p * (FOUR_PI_3 * R * R * R) / (mg * ph.Rg + m * ph.Rv);
+    const double Tbar = p * (FOUR_PI_3 * R * R * R) / fma(mg, ph.Rg, m * ph.Rv);
     const double chibar = m / (m + mg);
-    const double S = ph.pvRg + (p - ph.pv) * ph.Rv;
+    const double S = fma(p - ph.pv, ph.Rv, ph.pvRg);
     const double iS = frcp(S);
     const double chiw = ph.pvRg * iS;
     const double flux = ph.dbc * (S * S * ph.inv_RgRv2T0) / (p - ph.pv) * (chiw - chibar) * iR;
     const double dTdr = ph.betaT * (ph.T0 - Tbar) * iR;
-    pdot = ph.g3 * iR * (-V * p + ph.RvT0 * flux + ph.kh * dTdr);
+    pdot = ph.g3 * iR * fma(-V, p, fma(ph.RvT0, flux, ph.kh * dTdr));
     mdot = FOUR_PI * R * R * flux;
 }
 
-// Keller--Miksis wall acceleration for contents of pressure p changing at the rate pdot (transfer
-// contents); the R-ddot part of d(p_bw)/dt is moved to the left as above.
-__device__ inline double km_rddot_pb(const Phys &ph, double R, double V, double p, double pdot, double pinf,
-                                     double irho, double ic)
+// Keller--Miksis wall acceleration for contents of pressure p changing at the rate pdot (transfer contents).
+__device__ __forceinline__ double km_rddot_pb(const Phys &ph, double R, double V, double p, double pdot, double pinf,
+                                              double irho, double ic)
 {
-    double iR = frcp(R);
-    double pbw = p - ph.mu4 * V * iR - ph.sigma2 * iR;
-    double dpbw = pdot + (ph.mu4 * V * V * iR + ph.sigma2 * V * iR) * iR;
-    double irc = irho * ic;
-    double num = (1.0 + V * ic) * (pbw - pinf) * irho + R * dpbw * irc - 1.5 * V * V * (1.0 - V * ic * (1.0 / 3.0));
-    double den = R * (1.0 - V * ic) + ph.mu4 * irc;
-    return num * frcp(den);
+#pragma clang fp contract(off)
+    const double t = fma(ph.mu4, V, ph.sigma2) * frcp(R);
+    return km_accel(ph, R, V, p, fma(R, pdot, V * t), t, pinf, irho, ic);
 }
 
 template <typename T>

@@ -27,6 +27,31 @@ struct PL {
     static constexpr int COUNT = D + 6;
 };
 
+// One direction's part of a flux divergence, (lo - hi)/dx added to acc (first: acc is empty), and the RK
+// combine a un + b (u + dt L) (un is left out on the first stage): their operations are fixed, so that every
+// stage kernel gives the same bits.
+template <typename TF>
+__device__ __forceinline__ TF div_add(bool first, TF acc, TF lo, TF hi, TF inv_dx)
+{
+#pragma clang fp contract(off)
+    const TF d = lo - hi;
+    if (first) return d * inv_dx;
+    if constexpr (sizeof(TF) == 4) return fmaf(d, inv_dx, acc);
+    else return fma(d, inv_dx, acc);
+}
+
+__device__ __forceinline__ double rk_combine(double b, double dt, double L, double u)
+{
+#pragma clang fp contract(off)
+    return b * fma(dt, L, u);
+}
+
+__device__ __forceinline__ double add_plain(double a, double b)
+{
+#pragma clang fp contract(off)
+    return a + b;
+}
+
 enum PrimMode { PRIM_ONLY = 0, PRIM_CFL = 1, PRIM_MOMENTS = 2 };
 
 constexpr int PRIM_SLOTS = 8;   // threads per cell in the primitive pass
@@ -45,7 +70,7 @@ struct BinSums {
 // One bin's terms added to the sums.  Shared by the primitive pass and the epilogue of the fused
 // stage kernel, with its operation order fixed (explicit fused multiply-adds, no contraction), so both
 // give bitwise the same primitives.  C: the power's constant table (PPOW_TABLE, in LDS).
-template <bool PW>
+template <int PW>
 __device__ __forceinline__ void bin_add(BinSums &r, int i, double x, double y, double w, double pg0, double r0,
                                         int nb, const Phys &ph, const double *__restrict__ C)
 {
@@ -88,7 +113,7 @@ __device__ __forceinline__ BinSums bin_sums(const double *__restrict__ q, const 
             bin_add_tr(r, i, q[(iNR + i) * N + c], q[(iNV + i) * N + c], q[(iNP + i) * N + c], bins.w[i], nb);
         return r;
     }
-    constexpr bool PW = CT == CT_FIFTHS;
+    constexpr int PW = pw_of(CT);
     // The pass is bound by the latency of the bin loads: four bins' values are loaded together,
     // then summed one bin at a time in bin order (scheduling barriers keep the loads grouped and
     // the four sums apart, so registers stay few).
@@ -360,7 +385,7 @@ __device__ __forceinline__ void dt_block(Scalars *sc, double fixed_dt, double cf
     }
 }
 
-__global__ void __launch_bounds__(WMAX_SLOTS) k_dt(Scalars *sc, double fixed_dt, double cfl, double *user_dt)
+static __global__ void __launch_bounds__(WMAX_SLOTS) k_dt(Scalars *sc, double fixed_dt, double cfl, double *user_dt)
 {
     dt_block(sc, fixed_dt, cfl, user_dt);
 }

@@ -175,7 +175,7 @@ __global__ void __launch_bounds__(256) k_el_gather(const double *__restrict__ P,
 }
 
 // Dormand--Prince 5(4) step of (R, Rdot) (published tableau, 1980).
-template <bool PW>
+template <int PW>
 __device__ inline void dp54(const Phys &ph, double r0, double pg0, double pinf, double irho, double ic, double y0,
                             double y1, double h, double &r5, double &v5, double &r4, double &v4)
 {
@@ -222,7 +222,7 @@ struct ElOdeArgs {
     int *nsub;              // accumulated accepted sub-steps per bubble, or null
 };
 
-template <bool PW>
+template <int PW>
 __global__ void __launch_bounds__(256) k_el_ode(ElOdeArgs A, Phys ph, Scalars *sc)
 {
     const long long nb = A.nb;

@@ -42,7 +42,7 @@ __device__ __forceinline__ double step_factor3(double rtol, double err)
 
 // Adaptive integration of one bin over tau: (y0, y1) = (R, Rdot) in, advanced values out.
 // Returns the accepted sub-steps; raises E_SUBSTEP when the attempt budget runs out.
-template <bool PW>
+template <int PW>
 __device__ inline int bubble_bin(const Phys &ph, double &y0, double &y1, double r0, double pg0, double pl,
                                  double irhol, double ic, double tau, double rtol, double vfloor, int max_substeps,
                                  Scalars *sc, long long c, int i)
@@ -217,7 +217,7 @@ __device__ __forceinline__ void bubble_block(const BubbleArgs &A, const Grid &g,
                 q[(iNP + i) * N + c] = n * y[2];
                 q[(iNM + i) * N + c] = n * y[3];
             } else {
-                acc = bubble_bin<CT == CT_FIFTHS>(ph, y0, y1, bins.r0[i], bins.pg0[i], pl, irhol, ic, tau, A.rtol,
+                acc = bubble_bin<pw_of(CT)>(ph, y0, y1, bins.r0[i], bins.pg0[i], pl, irhol, ic, tau, A.rtol,
                                                   vfloor, A.max_substeps, sc, c, i);
             }
             q[(iNR + i) * N + c] = n * y0;

@@ -18,6 +18,7 @@
 
 #include "device_common.hpp"
 #include "ee_kernels.hpp"
+#include "stage_args.hpp"
 
 namespace bub {
 
@@ -101,30 +102,6 @@ struct Geo {
     }
 };
 
-// RK combine: out = a * un + b * (uk + dt * L); a == 0 skips un.  RHS mode writes L.
-struct StageArgs {
-    const double *qk;   // u^(k): stencil source
-    const double *qn;   // u^n (own cell only), may equal qk or be null when a == 0
-    double *qo;         // output
-    const double *P;    // primitive scratch of qk
-    const double *dtp;  // device step (RK mode)
-    double a, b;
-    int rhs_mode;       // 1: write L instead of the combine
-    int sources;        // 0: leave bubble source terms out (split mode flux part)
-    int ntile[3];
-    int nblk_per_xcd;
-    int ntiles;
-    int ngroups;        // workgroups per tile, each taking a contiguous range of bpg bins
-    int bpg;            // bins per group (ngroups * bpg >= nb)
-    int nitems;         // ntiles * ngroups
-    // Fused primitive pass (RK mode, one workgroup per tile): the epilogue writes the primitives of
-    // the state it produces into Pout (the layout of P; must not be P) and, with cfl set, posts that
-    // state's wave-speed maximum.  Null Pout: the next stage needs a primitive pass of its own.
-    double *Pout;
-    int cfl;
-    Scalars *sc;        // error word and wave-speed maxima of the context
-};
-
 // LDS needs of one tile: coef[F] and scr[SCR] of TF, flag[F] bytes.  NF: state fields per bin (2, or 4
 // for transfer contents), each with a line array and a face array.
 template <int D, int TX_, int TY_, int TZ_, typename TF, int NF = 2>
@@ -137,6 +114,79 @@ struct StageLds {
     static constexpr int BYTES = (G::F + SCR) * (int)sizeof(TF) + G::F;
 };
 
+// Mixture face between the cells f-1 and f of direction d: WENO5 of the primitives (ld(v, o): primitive v of
+// cell f - 3 + o; fl6: that cell is a mirrored ghost, whose normal velocity changes sign), admissibility
+// check, HLLC.  F_: the mixture fluxes; a bin variable's flux is coef times its value on the upwind side
+// (right: the cell f's side), coef = n_K (u_K + fac); ok false: the face takes cell values.
+template <int D, int d, typename TF, typename Ld>
+__device__ __forceinline__ void core_face(Ld &&ld, const bool (&fl6)[6], const Phys &ph, TF (&F_)[D + 3], TF &coef,
+                                          bool &right, bool &ok)
+{
+    constexpr int NC = D + 5;
+    const TF pinf = (TF)ph.pi_inf, gpi = (TF)ph.gpi, igm1 = (TF)ph.inv_gm1, gam = (TF)ph.gamma;
+    TF WL[NC], WR[NC], WcL[NC], WcR[NC];
+#pragma unroll
+    for (int v = 0; v < NC; ++v) {
+        TF s[6];
+#pragma unroll
+        for (int o = 0; o < 6; ++o) s[o] = ld(v, o);
+        if (v == 1 + d) {
+#pragma unroll
+            for (int o = 0; o < 6; ++o) s[o] = fl6[o] ? -s[o] : s[o];
+        }
+        weno5_pair(s, WL[v], WR[v]);
+        WcL[v] = s[2];
+        WcR[v] = s[3];
+    }
+    constexpr int iPL = D + 1, iA = D + 2, iN = D + 3, iB = D + 4;
+    ok = WL[0] > TF(0) && WR[0] > TF(0) && WL[iA] >= TF(0) && WL[iA] < TF(1) && WR[iA] >= TF(0) &&
+         WR[iA] < TF(1) && WL[iN] >= TF(0) && WR[iN] >= TF(0) && WL[iPL] + pinf > TF(0) &&
+              WR[iPL] + pinf > TF(0);
+    if (!ok) {
+#pragma unroll
+        for (int v = 0; v < NC; ++v) {
+            WL[v] = WcL[v];
+            WR[v] = WcR[v];
+        }
+    }
+    // HLLC (Davis speeds, Toro contact speed, difference-form star flux)
+    TF pK[2], EK[2], cK[2];
+    const TF *Ws[2] = {WL, WR};
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const TF *Wk = Ws[s];
+        TF a = Wk[iA], oma = TF(1) - a;
+        TF u2 = TF(0);
+#pragma unroll
+        for (int e = 0; e < D; ++e) u2 += Wk[1 + e] * Wk[1 + e];
+        pK[s] = oma * Wk[iPL] + a * Wk[iB];
+        EK[s] = oma * (Wk[iPL] + gpi) * igm1 + TF(0.5) * Wk[0] * u2;
+        cK[s] = tsqrt(gam * (Wk[iPL] + pinf) * oma * trcp(Wk[0]));
+    }
+    TF uL = WL[1 + d], uR = WR[1 + d];
+    TF SL = dmin(uL - cK[0], uR - cK[1]);
+    TF SR = dmax(uL + cK[0], uR + cK[1]);
+    TF mL = WL[0] * (SL - uL), mR = WR[0] * (SR - uR);
+    TF Ss = tdiv(pK[1] - pK[0] + uL * mL - uR * mR, mL - mR);
+    int side, star;
+    if (SL >= TF(0)) { side = 0; star = 0; }
+    else if (Ss >= TF(0)) { side = 0; star = 1; }
+    else if (SR > TF(0)) { side = 1; star = 1; }
+    else { side = 1; star = 0; }
+    const TF *WK = side ? WR : WL;
+    TF SK = side ? SR : SL;
+    TF un = WK[1 + d], rk = WK[0], pk = side ? pK[1] : pK[0], ek = side ? EK[1] : EK[0];
+    TF fac = star ? tdiv(SK * (Ss - un), SK - Ss) : TF(0);
+    F_[0] = rk * un + fac * rk;
+#pragma unroll
+    for (int e = 0; e < D; ++e)
+        F_[1 + e] = rk * un * WK[1 + e] + (e == d ? pk : TF(0)) + fac * rk * (e == d ? SK : WK[1 + e]);
+    F_[D + 1] = (ek + pk) * un + fac * (ek + pk + rk * Ss * (SK - un));
+    F_[D + 2] = WK[iA] * un + fac * WK[iA];
+    coef = WK[iN] * (un + fac);
+    right = side;
+}
+
 // The work of one tile (every thread of the workgroup calls it).  FUSE: the epilogue carries the
 // primitive pass of the state it writes (A.Pout, A.cfl).
 template <int D, int TX_, int TY_, int TZ_, int BLOCK, typename TF, bool FUSE, int CT>
@@ -148,9 +198,9 @@ __device__ __forceinline__ void stage_tile(const StageArgs &A, const Grid &g, co
                                            double *__restrict__ s_out, const double *__restrict__ s_pp)
 {
     using G = Geo<D, TX_, TY_, TZ_>;
-    constexpr int T = G::T, F = G::F, C = G::C, NC = G::NC, NCF = G::NCF, L = G::L;
+    constexpr int T = G::T, F = G::F, C = G::C, NCF = G::NCF;
     constexpr bool TR = CT == CT_TRANSFER;   // transfer contents: n p_b and n m_v per bin as well
-    constexpr bool PW = CT == CT_FIFTHS;
+    constexpr int PW = pw_of(CT);
     constexpr int CPT = (C + BLOCK - 1) / BLOCK;  // cross cells staged per thread
     const int tx = tile % A.ntile[0];
     const int ty = (tile / A.ntile[0]) % A.ntile[1];
@@ -159,7 +209,6 @@ __device__ __forceinline__ void stage_tile(const StageArgs &A, const Grid &g, co
     const long long N = g.N;
     const int nb = bins.nb;
     const int tid = threadIdx.x;
-    const TF pinf = (TF)ph.pi_inf, gpi = (TF)ph.gpi, igm1 = (TF)ph.inv_gm1, gam = (TF)ph.gamma;
 
     // ---- per-thread staging plan: global index, 1/n and line-array slots of its cross cells ----
     unsigned st_g[CPT];
@@ -218,72 +267,15 @@ __device__ __forceinline__ void stage_tile(const StageArgs &A, const Grid &g, co
                     fl6[o] = f;
                 }
             }
-            TF WL[NC], WR[NC], WcL[NC], WcR[NC];
-#pragma unroll
-            for (int v = 0; v < NC; ++v) {
-                TF s[6];
-#pragma unroll
-                for (int o = 0; o < 6; ++o) s[o] = (TF)A.P[(long long)v * N + gi6[o]];
-                if (v == 1 + d) {
-#pragma unroll
-                    for (int o = 0; o < 6; ++o) s[o] = fl6[o] ? -s[o] : s[o];
-                }
-                weno5_pair(s, WL[v], WR[v]);
-                WcL[v] = s[2];
-                WcR[v] = s[3];
-            }
-            constexpr int iPL = D + 1, iA = D + 2, iN = D + 3, iB = D + 4;
-            bool ok = WL[0] > TF(0) && WR[0] > TF(0) && WL[iA] >= TF(0) && WL[iA] < TF(1) && WR[iA] >= TF(0) &&
-                      WR[iA] < TF(1) && WL[iN] >= TF(0) && WR[iN] >= TF(0) && WL[iPL] + pinf > TF(0) &&
-                      WR[iPL] + pinf > TF(0);
-            if (!ok) {
-#pragma unroll
-                for (int v = 0; v < NC; ++v) {
-                    WL[v] = WcL[v];
-                    WR[v] = WcR[v];
-                }
-            }
-            // HLLC (Davis speeds, Toro contact speed, difference-form star flux)
-            TF pK[2], EK[2], cK[2];
-            const TF *Ws[2] = {WL, WR};
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                const TF *Wk = Ws[s];
-                TF a = Wk[iA], oma = TF(1) - a;
-                TF u2 = TF(0);
-#pragma unroll
-                for (int e = 0; e < D; ++e) u2 += Wk[1 + e] * Wk[1 + e];
-                pK[s] = oma * Wk[iPL] + a * Wk[iB];
-                EK[s] = oma * (Wk[iPL] + gpi) * igm1 + TF(0.5) * Wk[0] * u2;
-                cK[s] = tsqrt(gam * (Wk[iPL] + pinf) * oma * trcp(Wk[0]));
-            }
-            TF uL = WL[1 + d], uR = WR[1 + d];
-            TF SL = dmin(uL - cK[0], uR - cK[1]);
-            TF SR = dmax(uL + cK[0], uR + cK[1]);
-            TF mL = WL[0] * (SL - uL), mR = WR[0] * (SR - uR);
-            TF Ss = tdiv(pK[1] - pK[0] + uL * mL - uR * mR, mL - mR);
-            int side, star;
-            if (SL >= TF(0)) { side = 0; star = 0; }
-            else if (Ss >= TF(0)) { side = 0; star = 1; }
-            else if (SR > TF(0)) { side = 1; star = 1; }
-            else { side = 1; star = 0; }
-            const TF *WK = side ? WR : WL;
-            TF SK = side ? SR : SL;
-            TF un = WK[1 + d], rk = WK[0], pk = side ? pK[1] : pK[0], ek = side ? EK[1] : EK[0];
-            TF fac = star ? tdiv(SK * (Ss - un), SK - Ss) : TF(0);
-            TF F_[NCF];
-            F_[0] = rk * un + fac * rk;
-#pragma unroll
-            for (int e = 0; e < D; ++e)
-                F_[1 + e] = rk * un * WK[1 + e] + (e == d ? pk : TF(0)) + fac * rk * (e == d ? SK : WK[1 + e]);
-            F_[D + 1] = (ek + pk) * un + fac * (ek + pk + rk * Ss * (SK - un));
-            F_[D + 2] = WK[iA] * un + fac * WK[iA];
+            TF F_[NCF], coef;
+            bool right, ok;
+            core_face<D, d, TF>([&](int v, int o) { return (TF)A.P[(long long)v * N + gi6[o]]; }, fl6, ph, F_, coef,
+                                right, ok);
             const int slot = G::OFF[d] + t;
 #pragma unroll
             for (int v = 0; v < NCF; ++v) s_cf[v * F + slot] = F_[v];
-            // passive bin flux = coef * phi_K with coef = n_K (u_K + fac)
-            s_coef[slot] = WK[iN] * (un + fac);
-            s_flag[slot] = (unsigned char)(side | (ok ? 0 : 2));
+            s_coef[slot] = coef;
+            s_flag[slot] = (unsigned char)((right ? 1 : 0) | (ok ? 0 : 2));
         }
     };
     core_faces(std::integral_constant<int, 0>{});
@@ -336,7 +328,8 @@ __device__ __forceinline__ void stage_tile(const StageArgs &A, const Grid &g, co
         for (int v = 0; v < NCF; ++v) {
             TF acc = TF(0);
 #pragma unroll
-            for (int d = 0; d < D; ++d) acc += (s_cf[v * F + flo[d]] - s_cf[v * F + fhi[d]]) * (TF)g.inv_dx[d];
+            for (int d = 0; d < D; ++d)
+                acc = div_add(d == 0, acc, s_cf[v * F + flo[d]], s_cf[v * F + fhi[d]], (TF)g.inv_dx[d]);
             Lc[v] = acc;
         }
         double nq[NCF];
@@ -344,11 +337,11 @@ __device__ __forceinline__ void stage_tile(const StageArgs &A, const Grid &g, co
         for (int v = 0; v < NCF; ++v) {
             long long o = (long long)v * N + gc;
             double Lv = (double)Lc[v];
-            if (v == D + 2 && A.sources) Lv += A.P[PL<D>::SA * N + gc];
+            if (v == D + 2 && A.sources) Lv = add_plain(Lv, A.P[PL<D>::SA * N + gc]);
             if (A.rhs_mode) A.qo[o] = Lv;
             else {
-                double r = A.b * (A.qk[o] + dt * Lv);
-                if (A.a != 0.0) r += A.a * A.qn[o];
+                double r = rk_combine(A.b, dt, Lv, A.qk[o]);
+                if (A.a != 0.0) r = fma(A.a, A.qn[o], r);
                 A.qo[o] = r;
                 nq[v] = r;
             }
@@ -530,11 +523,11 @@ __device__ __forceinline__ void stage_tile(const StageArgs &A, const Grid &g, co
             [[maybe_unused]] TF LPf = TF(0), LMf = TF(0);
 #pragma unroll
             for (int d = 0; d < D; ++d) {
-                LRf += (s_fR[flo[d]] - s_fR[fhi[d]]) * (TF)g.inv_dx[d];
-                LVf += (s_fV[flo[d]] - s_fV[fhi[d]]) * (TF)g.inv_dx[d];
+                LRf = div_add(d == 0, LRf, s_fR[flo[d]], s_fR[fhi[d]], (TF)g.inv_dx[d]);
+                LVf = div_add(d == 0, LVf, s_fV[flo[d]], s_fV[fhi[d]], (TF)g.inv_dx[d]);
                 if constexpr (TR) {
-                    LPf += (s_fP[flo[d]] - s_fP[fhi[d]]) * (TF)g.inv_dx[d];
-                    LMf += (s_fM[flo[d]] - s_fM[fhi[d]]) * (TF)g.inv_dx[d];
+                    LPf = div_add(d == 0, LPf, s_fP[flo[d]], s_fP[fhi[d]], (TF)g.inv_dx[d]);
+                    LMf = div_add(d == 0, LMf, s_fM[flo[d]], s_fM[fhi[d]], (TF)g.inv_dx[d]);
                 }
             }
             double LR = (double)LRf, LV = (double)LVf;
@@ -543,33 +536,33 @@ __device__ __forceinline__ void stage_tile(const StageArgs &A, const Grid &g, co
             if (A.sources && own_n > 0.0) {
                 // Keller--Miksis in FP64 from the FP64 state of the owned cell
                 double own_R = xr0 * own_in, own_V = xv0 * own_in;
-                LR += own_n * own_V;
+                LR = fma(own_n, own_V, LR);
                 if constexpr (TR) {
                     const double own_P = own_p * own_in, own_M = own_m * own_in;
                     double pdot, mdot;
                     contents_rates(ph, own_R, own_V, own_P, own_M, bins.mg[ib], pdot, mdot);
-                    LV += own_n * km_rddot_pb(ph, own_R, own_V, own_P, pdot, own_pl, own_irhol, own_ic);
-                    LP_ += own_n * pdot;
-                    LM_ += own_n * mdot;
+                    LV = fma(own_n, km_rddot_pb(ph, own_R, own_V, own_P, pdot, own_pl, own_irhol, own_ic), LV);
+                    LP_ = fma(own_n, pdot, LP_);
+                    LM_ = fma(own_n, mdot, LM_);
                 } else {
-                    LV += own_n * km_rddot_t<PW>(ph, own_R, own_V, r0, pg0, own_pl, own_irhol, own_ic, s_pp);
+                    LV = fma(own_n, km_rddot_t<PW>(ph, own_R, own_V, r0, pg0, own_pl, own_irhol, own_ic, s_pp), LV);
                 }
             }
             double xr = LR, xv = LV;
             [[maybe_unused]] double xp = LP_, xm = LM_;
             if (!A.rhs_mode) {
-                xr = A.b * (xr0 + dt * LR);
-                xv = A.b * (xv0 + dt * LV);
+                xr = rk_combine(A.b, dt, LR, xr0);
+                xv = rk_combine(A.b, dt, LV, xv0);
                 if constexpr (TR) {
-                    xp = A.b * (own_p + dt * LP_);
-                    xm = A.b * (own_m + dt * LM_);
+                    xp = rk_combine(A.b, dt, LP_, own_p);
+                    xm = rk_combine(A.b, dt, LM_, own_m);
                 }
                 if (A.a != 0.0) {
-                    xr += A.a * own_nr;   // u^n of bin ib at the owned cell
-                    xv += A.a * own_nv;
+                    xr = fma(A.a, own_nr, xr);   // u^n of bin ib at the owned cell
+                    xv = fma(A.a, own_nv, xv);
                     if constexpr (TR) {
-                        xp += A.a * own_np;
-                        xm += A.a * own_nm;
+                        xp = fma(A.a, own_np, xp);
+                        xm = fma(A.a, own_nm, xm);
                     }
                 }
             }
