@@ -4,10 +4,12 @@
 """
 from __future__ import annotations
 
+import concurrent.futures
 import glob
 import os
 import subprocess
 import sys
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -15,7 +17,7 @@ SO = os.path.join(HERE, "libbubbly.so")
 ARCH = "gfx950"
 
 FLAGS = [
-    "-O3", "-std=c++17", "-fPIC", "-shared", f"--offload-arch={ARCH}",
+    "-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
     # packed FP32 instructions are kept out of every kernel on this target
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wno-unused-command-line-argument",
@@ -26,15 +28,25 @@ def sources():
     return sorted(glob.glob(os.path.join(HERE, "csrc", "*.hip")))
 
 
-def build(verbose: bool = False, extra=None) -> str:
-    cmd = ["hipcc"] + FLAGS + (extra or []) + ["-I", os.path.join(ROOT, "include"),
-                                               "-I", os.path.join(HERE, "csrc")] + sources() + ["-o", SO + ".tmp"]
+def _run(cmd, verbose):
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         sys.stderr.write(res.stdout + res.stderr)
         raise RuntimeError("hipcc failed building libbubbly.so")
+
+
+def build(verbose: bool = False, extra=None) -> str:
+    """Compile every source (at the same time, each to its own object) and link them."""
+    inc = ["-I", os.path.join(ROOT, "include"), "-I", os.path.join(HERE, "csrc")]
+    srcs = sources()
+    with tempfile.TemporaryDirectory() as tmp:
+        objs = [os.path.join(tmp, os.path.basename(s) + ".o") for s in srcs]
+        cmds = [["hipcc"] + FLAGS + (extra or []) + inc + ["-c", s, "-o", o] for s, o in zip(srcs, objs)]
+        with concurrent.futures.ThreadPoolExecutor(len(srcs)) as ex:
+            list(ex.map(lambda c: _run(c, verbose), cmds))
+        _run(["hipcc", "-shared", f"--offload-arch={ARCH}"] + objs + ["-o", SO + ".tmp"], verbose)
     os.replace(SO + ".tmp", SO)
     return SO
 

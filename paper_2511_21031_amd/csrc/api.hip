@@ -21,6 +21,7 @@
 #include "batch_plan.hpp"
 #include "viscous_kernel.hpp"
 #include "source_kernel.hpp"
+#include "line.hpp"
 
 #include <vector>
 #include "ctx.hpp"
@@ -112,7 +113,8 @@ template <> struct Tile<2, 4> { static constexpr int TX = 32, TY = 15, TZ = 1, B
 template <> struct Tile<2, 5> { static constexpr int TX = 16, TY = 15, TZ = 1, BLOCK = 256; };
 template <> struct Tile<3, 3> { static constexpr int TX = 8, TY = 8, TZ = 3, BLOCK = 256; };
 template <> struct Tile<3, 4> { static constexpr int TX = 8, TY = 8, TZ = 7, BLOCK = 512; };
-constexpr int TILE_COUNT[4] = {0, 3, 6, 5};
+constexpr int TILE_COUNT[4] = {0, 4, 6, 5};
+constexpr int LINE_SHAPE = 3;   // the last 1D shape: one wave per tile of 63 cells (line_kernel.hpp)
 
 template <int D, int V>
 void tile_info(int *tx, int *ty, int *tz, int *block)
@@ -134,6 +136,17 @@ int ct_of(const bub_ctx *c)
     return c->ph.pw_c > 0 ? CT_FIFTHS : CT_POLY;
 }
 bool pw_fast(const bub_ctx *c) { return ct_of(c) == CT_FIFTHS; }
+
+// The stage shape of a context: the one set, or by default the wave tiles of 1D grids where they apply, else
+// shape 0.
+int shape_of(const bub_ctx *c)
+{
+    if (c->tile >= 0) return c->tile;
+    return pw_fast(c) && line_ok(c) ? LINE_SHAPE : 0;
+}
+
+// Whether its stages run the wave tiles (1D transfer contents always do).
+bool uses_line(const bub_ctx *c) { return line_ok(c) && (!pw_fast(c) || shape_of(c) == LINE_SHAPE); }
 
 template <int D, int S, int CELLS, int CT>
 void launch_prim_p(bub_ctx *c, const double *q, double *out, int mode, hipStream_t s)
@@ -304,7 +317,13 @@ int prim(bub_ctx *c, const double *q, double *out, int mode, hipStream_t s)
 
 int stage_kernel(bub_ctx *c, const StageArgs &A, hipStream_t s)
 {
-    const int v = pw_fast(c) ? c->tile : 0;
+    if (uses_line(c)) {
+        long pr = prof_begin(c, BUB_K_STAGE, s);
+        const int rc = launch_line(c, A, s);
+        prof_end(c, pr, s);
+        return rc;
+    }
+    const int v = pw_fast(c) ? shape_of(c) : 0;
     switch (c->ndim) {
     case 1:
         if (v == 1) return launch_stage_v<1, 1>(c, A, s);
@@ -400,7 +419,7 @@ int stage(bub_ctx *c, const StageArgs &A, hipStream_t s, double tc)
 long long stage_tiles(const bub_ctx *c)
 {
     int tx, ty, tz, blk;
-    bub_tile_info(c, c->tile, &tx, &ty, &tz, &blk);
+    bub_tile_info(c, shape_of(c), &tx, &ty, &tz, &blk);
     return (long long)((c->g.n[0] + tx - 1) / tx) * ((c->g.n[1] + ty - 1) / ty) * ((c->g.n[2] + tz - 1) / tz);
 }
 
@@ -414,8 +433,9 @@ bool stage_fusable(const bub_ctx *c)
     // 3D FP64: the epilogue's registers cost the stage more than the pass it saves (measured at 256^3
     // x 21 bins: 13.6 ms fused against 11.9 + 1.5 ms)
     if (c->ndim == 3 && c->opts.precision == BUB_PREC_FP64) return false;
-    int groups = 0;
-    bin_grouping(c, stage_tiles(c), &groups);
+    int groups = 0, nt;
+    if (uses_line(c)) line_grouping(c, &nt, &groups);
+    else bin_grouping(c, stage_tiles(c), &groups);
     return groups == 1;
 }
 
@@ -1194,6 +1214,7 @@ int bub_tile_info(const bub_ctx *c, int idx, int *tx, int *ty, int *tz, int *blo
     case 10: tile_info<1, 0>(tx, ty, tz, block); break;
     case 11: tile_info<1, 1>(tx, ty, tz, block); break;
     case 12: tile_info<1, 2>(tx, ty, tz, block); break;
+    case 10 + LINE_SHAPE: *tx = 63, *ty = *tz = 1, *block = 64; break;
     case 20: tile_info<2, 0>(tx, ty, tz, block); break;
     case 21: tile_info<2, 1>(tx, ty, tz, block); break;
     case 22: tile_info<2, 2>(tx, ty, tz, block); break;
@@ -1213,6 +1234,7 @@ int bub_tile_set(bub_ctx *c, int idx)
 {
     if (!c || idx < 0 || idx >= TILE_COUNT[c->ndim]) return BUB_EINVAL;
     if (idx != 0 && !pw_fast(c)) return BUB_EUNSUPPORTED;
+    if (c->ndim == 1 && idx == LINE_SHAPE && !line_ok(c)) return BUB_EUNSUPPORTED;
     c->tile = idx;
     return BUB_OK;
 }
@@ -1220,7 +1242,7 @@ int bub_tile_set(bub_ctx *c, int idx)
 int bub_tile_get(const bub_ctx *c, int *idx)
 {
     if (!c || !idx) return BUB_EINVAL;
-    *idx = c->tile;
+    *idx = shape_of(c);
     return BUB_OK;
 }
 
@@ -1329,7 +1351,7 @@ int bub_autotune(bub_ctx *c, const double *q, double *scratch, int reps, double 
     c->prof_on = 0;
     double best_ms = 1e300;
     int best_v = keep;
-    const int nshape = pw_fast(c) ? TILE_COUNT[c->ndim] : 1;
+    const int nshape = !pw_fast(c) ? 1 : TILE_COUNT[c->ndim] - (c->ndim == 1 && !line_ok(c));
     if (ms_out)
         for (int v = nshape; v < TILE_COUNT[c->ndim]; ++v) ms_out[v] = -1.0;
     for (int v = 0; v < nshape && rc == BUB_OK; ++v) {
@@ -1356,7 +1378,7 @@ int bub_autotune(bub_ctx *c, const double *q, double *scratch, int reps, double 
     (void)hipEventDestroy(e1);
     c->prof_on = prof;
     c->tile = rc == BUB_OK ? best_v : keep;
-    if (best) *best = c->tile;
+    if (best) *best = shape_of(c);
     return rc;
 }
 
@@ -1881,7 +1903,7 @@ int member_desc(const bub_batch::Member &m, BatchMember *d)
     d->max_substeps = c->opts.max_substeps > 0 ? c->opts.max_substeps : 10000;
     d->sources = c->opts.bubble_mode == BUB_BUBBLES_UNSPLIT;
     int tx, ty, tz, blk;
-    if (bub_tile_info(c, c->tile, &tx, &ty, &tz, &blk)) return BUB_EINVAL;
+    if (bub_tile_info(c, shape_of(c), &tx, &ty, &tz, &blk)) return BUB_EINVAL;
     d->ntile[0] = (c->g.n[0] + tx - 1) / tx;
     d->ntile[1] = (c->g.n[1] + ty - 1) / ty;
     d->ntile[2] = (c->g.n[2] + tz - 1) / tz;
@@ -1910,7 +1932,7 @@ int batch_rebuild(bub_batch *b, hipStream_t s)
         if (rc) return rc;
         const bub_ctx *c = m.ctx;
         const int S = slots_for(c->N);
-        pm.push_back({(int)i, c->ndim, S, c->tile, c->opts.bubble_mode == BUB_BUBBLES_SPLIT,
+        pm.push_back({(int)i, c->ndim, S, shape_of(c), c->opts.bubble_mode == BUB_BUBBLES_SPLIT,
                       (c->N + cells_for(S) - 1) / cells_for(S), (long long)tab[i].nitems});
     }
     BatchPlan plan;

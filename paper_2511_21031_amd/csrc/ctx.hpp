@@ -32,7 +32,7 @@ struct bub_ctx {
     bub::Grid g{};
     bub::Bins bt{};
     bool owns = true;            // device buffers allocated (and freed) by the library
-    int tile = 0;                // stage-kernel tile shape (index into the per-dimension list)
+    int tile = -1;               // stage-kernel tile shape (index into the per-dimension list; -1: by rule)
     int bin_groups = 0;          // stage-kernel workgroups per tile (0: chosen per launch from the tile count)
     int32_t *nsub_diag = nullptr;   // split-mode steps record their sub-step counts here ([2][nb][N])
     bool src_on = false;         // one-way acoustic source set (bub_set_source)

@@ -1,0 +1,79 @@
+"""Right-hand sides and steps of the stage kernels at the sizes where their tilings can go wrong: just below, at and
+just above one and two tiles, the smallest grids, cells without bubbles, every kind of end, both contents.
+
+The oracle is the reference; the tolerance is that of the other right-hand-side tests (rounding of face fluxes,
+1e-12 of the flux-divergence scale).  Steps of different shapes have to agree bit for bit.
+"""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import workloads as W
+from tests.parity import flux_scale, perturb_bins, rhs_err
+
+pytestmark = pytest.mark.gpu
+RHS_TOL = 1e-12
+
+LINE = [((3,), 1), ((62,), 0), ((63,), 1), ((64,), 2), ((126,), 0), ((127,), 2), ((190,), 1)]
+
+
+@pytest.fixture(scope="module")
+def torch():
+    t = pytest.importorskip("torch")
+    if not t.cuda.is_available():
+        pytest.skip("no GPU")
+    return t
+
+
+@pytest.fixture(scope="module")
+def bub(torch):
+    import paper_2511_21031_amd as B
+    B.lib()
+    return B
+
+
+def _case(n, bc, contents, nb):
+    case = W.random_smooth(len(n), n, 1e-4, nb, seed=31 + sum(n), bc=bc)
+    if contents:
+        case = dataclasses.replace(case, gas=dict(W.AIR_WITH_VAPOUR), contents=dict(W.AIR_VAPOUR))
+    return case
+
+
+def _state(orc, pb, case, bubbles_everywhere=True):
+    if not bubbles_everywhere:   # a stretch of pure liquid that starts and ends inside tiles
+        a = case.prim[case.ndim + 2]
+        a[len(a) // 3:len(a) // 2] = 0.0
+    return perturb_bins(orc.init_state(pb, case.prim), case.ndim, case.nb, seed=6)
+
+
+def _check(torch, bub, orc, n, bc, contents, nb, everywhere):
+    case = _case(n, bc, contents, nb)
+    pb = orc.problem_from_case(case)
+    q = _state(orc, pb, case, everywhere)
+    ref = orc.rhs(pb, q)
+    ctx = bub.context_from_case(case)
+    qg = torch.from_numpy(q).cuda()
+    err = rhs_err(ctx.rhs_stage(qg).cpu().numpy(), ref, flux_scale(orc, pb, q))
+    assert err.max() < RHS_TOL, (n, bc, err)
+    assert ctx.last_error()[0] == 0
+
+
+@pytest.mark.parametrize("contents", [False, True])
+@pytest.mark.parametrize("n,bc", LINE)
+def test_line_tiles(torch, bub, orc, n, bc, contents):
+    _check(torch, bub, orc, n, bc, contents, 5, everywhere=bc != 0)
+
+
+def test_large_1d_grid_carries_its_primitives(torch, bub):
+    """2^19 cells: the wave tiles' stages write the next state's primitives; bitwise the tiles of 255 cells."""
+    case = W.random_smooth(1, ((1 << 19) + 5,), 1e-4, 3, seed=44)
+    outs = []
+    for tile in (3, 0):
+        ctx = bub.context_from_case(case)
+        ctx.tile = tile
+        q = ctx.init_state(torch.from_numpy(case.prim).cuda())
+        ctx.rk3_steps(q, ctx.new_work(), 2)
+        assert ctx.last_error()[0] == 0
+        outs.append(q)
+    assert torch.equal(outs[0], outs[1])
