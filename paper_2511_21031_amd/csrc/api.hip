@@ -22,6 +22,7 @@
 #include "viscous_kernel.hpp"
 #include "source_kernel.hpp"
 #include "line.hpp"
+#include "tile.hpp"
 
 #include <vector>
 #include "ctx.hpp"
@@ -128,8 +129,8 @@ void tile_info(int *tx, int *ty, int *tz, int *block)
 // The kernels are compiled for the bubble contents (Contents): polytropic gas whose power x^(3 kappa)
 // takes the fifth-root Newton form when 3 kappa is a whole number of fifths (air's 4.2, 3, 5, ...) or the
 // general exp2(3 kappa log2 x) form otherwise, or transfer contents.  Only the fifth-root form has every
-// stage shape; the others run stage shape 0, transfer contents with the fused epilogue where it applies,
-// the general power with the separate primitive pass.
+// stage shape, air and transfer contents kernels of their own (line_kernel.hpp, tile_kernel.hpp); the general
+// power runs stage shape 0 with the separate primitive pass.
 int ct_of(const bub_ctx *c)
 {
     if (c->opts.contents == BUB_CONTENTS_TRANSFER) return CT_TRANSFER;
@@ -137,16 +138,29 @@ int ct_of(const bub_ctx *c)
 }
 bool pw_fast(const bub_ctx *c) { return ct_of(c) == CT_FIFTHS; }
 
-// The stage shape of a context: the one set, or by default the wave tiles of 1D grids where they apply, else
-// shape 0.
+// The stage shape of a context: the one set, or by default the best one for polytropic air.
+// In 3D FP64 8 x 8 x 3 on 256 threads is best (256^3 x 21: 10.6 ms against 11.4 ms for 8 x 8 x 7 on 512), in
+// mixed precision 8 x 8 x 7 (8.6 against 9.9 ms); in 2D 16 x 15 in both (1024^2 x 31: 0.633 and 0.570 ms against
+// 0.636 and 0.581 ms for 32 x 15).
+int air_shape(const bub_ctx *c)
+{
+    if (c->ndim == 1) return LINE_SHAPE;
+    if (c->ndim == 2) return 5;
+    return c->opts.precision == BUB_PREC_MIXED && ct_of(c) != CT_TRANSFER ? 4 : 3;
+}
 int shape_of(const bub_ctx *c)
 {
     if (c->tile >= 0) return c->tile;
-    return pw_fast(c) && line_ok(c) ? LINE_SHAPE : 0;
+    if (!pw_fast(c)) return 0;
+    const int v = air_shape(c);
+    return (c->ndim == 1 ? line_ok(c) : tile_ok(c, v)) ? v : 0;
 }
 
-// Whether its stages run the wave tiles (1D transfer contents always do).
-bool uses_line(const bub_ctx *c) { return line_ok(c) && (!pw_fast(c) || shape_of(c) == LINE_SHAPE); }
+// The shape whose kernel its stages run (transfer contents, listed with shape 0 only, have one of their own).
+int kernel_shape(const bub_ctx *c) { return ct_of(c) == CT_TRANSFER ? air_shape(c) : pw_fast(c) ? shape_of(c) : 0; }
+
+// Whether its stages run the wave tiles of 1D grids.
+bool uses_line(const bub_ctx *c) { return line_ok(c) && kernel_shape(c) == LINE_SHAPE; }
 
 template <int D, int S, int CELLS, int CT>
 void launch_prim_p(bub_ctx *c, const double *q, double *out, int mode, hipStream_t s)
@@ -219,21 +233,19 @@ int launch_stage_t(bub_ctx *c, StageArgs A, hipStream_t s)
     if (A.Pout && A.ngroups != 1) return BUB_EINVAL;   // the fused epilogue needs every bin of a cell
     A.nitems = A.ntiles * A.ngroups;
     A.nblk_per_xcd = (A.nitems + 7) / 8;
+    if (tile_ok(c, V)) {
+        long pr = prof_begin(c, BUB_K_STAGE, s);
+        const int rc = launch_tile(c, V, A, s);
+        prof_end(c, pr, s);
+        return rc;
+    }
     const dim3 grid(8 * A.nblk_per_xcd), block(TC::BLOCK);
-    if (!pw_fast(c)) {
+    if (!pw_fast(c)) {   // the general power: shape 0, with the separate primitive pass
         if constexpr (V == 0) {
-            const bool tr = ct_of(c) == CT_TRANSFER;
-            if (A.Pout && !tr) return BUB_EINVAL;   // (stage_fusable is false for the general power)
+            if (A.Pout) return BUB_EINVAL;   // (stage_fusable is false for it)
             long pr = prof_begin(c, BUB_K_STAGE, s);
-            if (tr && A.Pout)
-                hipLaunchKernelGGL((k_stage<D, TC::TX, TC::TY, TC::TZ, TC::BLOCK, TF, true, CT_TRANSFER>), grid,
-                                   block, 0, s, A, c->g, c->ph, c->bt);
-            else if (tr)
-                hipLaunchKernelGGL((k_stage<D, TC::TX, TC::TY, TC::TZ, TC::BLOCK, TF, false, CT_TRANSFER>), grid,
-                                   block, 0, s, A, c->g, c->ph, c->bt);
-            else
-                hipLaunchKernelGGL((k_stage<D, TC::TX, TC::TY, TC::TZ, TC::BLOCK, TF, false, CT_POLY>), grid, block,
-                                   0, s, A, c->g, c->ph, c->bt);
+            hipLaunchKernelGGL((k_stage<D, TC::TX, TC::TY, TC::TZ, TC::BLOCK, TF, false, CT_POLY>), grid, block, 0, s, A,
+                               c->g, c->ph, c->bt);
             prof_end(c, pr, s);
             return hipGetLastError() == hipSuccess ? BUB_OK : BUB_EHIP;
         }
@@ -323,7 +335,7 @@ int stage_kernel(bub_ctx *c, const StageArgs &A, hipStream_t s)
         prof_end(c, pr, s);
         return rc;
     }
-    const int v = pw_fast(c) ? shape_of(c) : 0;
+    const int v = kernel_shape(c);
     switch (c->ndim) {
     case 1:
         if (v == 1) return launch_stage_v<1, 1>(c, A, s);
@@ -419,7 +431,7 @@ int stage(bub_ctx *c, const StageArgs &A, hipStream_t s, double tc)
 long long stage_tiles(const bub_ctx *c)
 {
     int tx, ty, tz, blk;
-    bub_tile_info(c, shape_of(c), &tx, &ty, &tz, &blk);
+    bub_tile_info(c, kernel_shape(c), &tx, &ty, &tz, &blk);
     return (long long)((c->g.n[0] + tx - 1) / tx) * ((c->g.n[1] + ty - 1) / ty) * ((c->g.n[2] + tz - 1) / tz);
 }
 

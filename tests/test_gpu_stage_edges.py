@@ -77,3 +77,13 @@ def test_large_1d_grid_carries_its_primitives(torch, bub):
         assert ctx.last_error()[0] == 0
         outs.append(q)
     assert torch.equal(outs[0], outs[1])
+
+
+PLANE = [((16, 15), 0), ((17, 16), 1), ((15, 14), 2), ((32, 30), 1), ((33, 31), 0), ((3, 3), 1), ((2, 40), 0), ((49, 7), 2)]
+BOX = [((8, 8, 3), 0), ((9, 9, 4), 1), ((7, 7, 2), 2), ((16, 8, 7), 1), ((17, 10, 8), 0), ((3, 3, 3), 1)]
+
+
+@pytest.mark.parametrize("contents", [False, True])
+@pytest.mark.parametrize("n,bc", PLANE + BOX)
+def test_balanced_tiles(torch, bub, orc, n, bc, contents):
+    _check(torch, bub, orc, n, bc, contents, 5 if len(n) == 2 else 3, everywhere=bc != 0)
