@@ -137,6 +137,8 @@ int ct_of(const bub_ctx *c)
     return c->ph.pw_c > 0 ? CT_FIFTHS : CT_POLY;
 }
 bool pw_fast(const bub_ctx *c) { return ct_of(c) == CT_FIFTHS; }
+// The same with polytropic air apart (primitive pass, bubble half-steps: its power without a branch).
+int ct_air(const bub_ctx *c) { return pw_fast(c) && c->ph.pw_c == 5 && c->ph.pw_d == 4 ? CT_AIR : ct_of(c); }
 
 // The stage shape of a context: the one set, or by default the best one for polytropic air.
 // In 3D FP64 8 x 8 x 3 on 256 threads is best (256^3 x 21: 10.6 ms against 11.4 ms for 8 x 8 x 7 on 512), in
@@ -150,7 +152,8 @@ int air_shape(const bub_ctx *c)
 }
 int shape_of(const bub_ctx *c)
 {
-    if (c->tile >= 0) return c->tile;
+    // (a batch applies one shape to a whole class, whose members need not all have it)
+    if (c->tile >= 0 && !(c->ndim == 1 && c->tile == LINE_SHAPE && !line_ok(c))) return c->tile;
     if (!pw_fast(c)) return 0;
     const int v = air_shape(c);
     return (c->ndim == 1 ? line_ok(c) : tile_ok(c, v)) ? v : 0;
@@ -180,7 +183,8 @@ void launch_prim_p(bub_ctx *c, const double *q, double *out, int mode, hipStream
 template <int D, int S, int CELLS>
 void launch_prim_s(bub_ctx *c, const double *q, double *out, int mode, hipStream_t s)
 {
-    switch (ct_of(c)) {
+    switch (ct_air(c)) {
+    case CT_AIR: launch_prim_p<D, S, CELLS, CT_AIR>(c, q, out, mode, s); break;
     case CT_FIFTHS: launch_prim_p<D, S, CELLS, CT_FIFTHS>(c, q, out, mode, s); break;
     case CT_TRANSFER: launch_prim_p<D, S, CELLS, CT_TRANSFER>(c, q, out, mode, s); break;
     default: launch_prim_p<D, S, CELLS, CT_POLY>(c, q, out, mode, s); break;
@@ -269,36 +273,54 @@ int launch_stage_v(bub_ctx *c, StageArgs A, hipStream_t s)
     return launch_stage_t<D, V, double>(c, A, s);
 }
 
-template <int D, int S, int CELLS>
-void launch_bubble_s(bub_ctx *c, const BubbleArgs &B, hipStream_t s)
+template <int D, int S, int CELLS, int CT>
+void launch_bubble_p(bub_ctx *c, const BubbleArgs &B, int mode, hipStream_t s)
 {
     const dim3 grid((unsigned)((c->g.N + CELLS - 1) / CELLS)), block(S * CELLS);
-    switch (ct_of(c)) {
-    case CT_FIFTHS:
-        hipLaunchKernelGGL((k_bubble<D, S, CELLS, CT_FIFTHS>), grid, block, 0, s, B, c->g, c->ph, c->bt, c->d_sc);
-        break;
-    case CT_TRANSFER:
-        hipLaunchKernelGGL((k_bubble<D, S, CELLS, CT_TRANSFER>), grid, block, 0, s, B, c->g, c->ph, c->bt, c->d_sc);
-        break;
-    default:
-        hipLaunchKernelGGL((k_bubble<D, S, CELLS, CT_POLY>), grid, block, 0, s, B, c->g, c->ph, c->bt, c->d_sc);
-        break;
+    if constexpr (CT != CT_POLY) {
+        if (mode == PRIM_CFL) {
+            hipLaunchKernelGGL((k_bubble<D, S, CELLS, CT, PRIM_CFL>), grid, block, 0, s, B, c->g, c->ph, c->bt, c->d_sc);
+            return;
+        }
+        if (mode == PRIM_ONLY) {
+            hipLaunchKernelGGL((k_bubble<D, S, CELLS, CT, PRIM_ONLY>), grid, block, 0, s, B, c->g, c->ph, c->bt, c->d_sc);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_bubble<D, S, CELLS, CT, BUBBLE_ONLY>), grid, block, 0, s, B, c->g, c->ph, c->bt, c->d_sc);
+}
+
+template <int D, int S, int CELLS>
+void launch_bubble_s(bub_ctx *c, const BubbleArgs &B, int mode, hipStream_t s)
+{
+    switch (ct_air(c)) {
+    case CT_AIR: launch_bubble_p<D, S, CELLS, CT_AIR>(c, B, mode, s); break;
+    case CT_FIFTHS: launch_bubble_p<D, S, CELLS, CT_FIFTHS>(c, B, mode, s); break;
+    case CT_TRANSFER: launch_bubble_p<D, S, CELLS, CT_TRANSFER>(c, B, mode, s); break;
+    default: launch_bubble_p<D, S, CELLS, CT_POLY>(c, B, mode, s); break;
     }
 }
 
 template <int D>
-void launch_bubble_d(bub_ctx *c, const BubbleArgs &B, hipStream_t s)
+void launch_bubble_d(bub_ctx *c, const BubbleArgs &B, int mode, hipStream_t s)
 {
     switch (slots_for(c->g.N)) {
-    case 1: launch_bubble_s<D, 1, 256>(c, B, s); break;
-    case 2: launch_bubble_s<D, 2, 64>(c, B, s); break;
-    case 4: launch_bubble_s<D, 4, 64>(c, B, s); break;
-    default: launch_bubble_s<D, 8, 64>(c, B, s); break;
+    case 1: launch_bubble_s<D, 1, 256>(c, B, mode, s); break;
+    case 2: launch_bubble_s<D, 2, 64>(c, B, mode, s); break;
+    case 4: launch_bubble_s<D, 4, 64>(c, B, mode, s); break;
+    default: launch_bubble_s<D, 8, 64>(c, B, mode, s); break;
     }
 }
 
-int bubble(bub_ctx *c, double *q, const double *taup, double tau_scale, double tau_fixed, int *nsub,
-           hipStream_t s)
+// Whether a bubble half-step can make the primitive pass of the state it leaves (the general power's sums take
+// another form of the power than its sub-steps).
+bool bubble_prims(const bub_ctx *c) { return ct_of(c) != CT_POLY; }
+
+// A bubble half-step; with Pout (bubble_prims) it also makes the primitive pass of its result into Pout, mode
+// PRIM_ONLY or PRIM_CFL.  n: the number density of q where the primitives of q are at hand (Pout may be their
+// scratch: a cell's n is read before its primitives are written), or null.
+int bubble(bub_ctx *c, double *q, const double *taup, double tau_scale, double tau_fixed, int *nsub, double *Pout,
+           int mode, const double *n, hipStream_t s)
 {
     BubbleArgs B{};
     B.q = q;
@@ -308,11 +330,14 @@ int bubble(bub_ctx *c, double *q, const double *taup, double tau_scale, double t
     B.rtol = c->opts.sub_rtol > 0.0 ? c->opts.sub_rtol : 1e-4;
     B.max_substeps = c->opts.max_substeps > 0 ? c->opts.max_substeps : 10000;
     B.nsub = nsub;
+    B.Pout = Pout;
+    B.n = n;
+    if (!Pout) mode = BUBBLE_ONLY;
     long pr = prof_begin(c, BUB_K_OTHER, s);
     switch (c->ndim) {
-    case 1: launch_bubble_d<1>(c, B, s); break;
-    case 2: launch_bubble_d<2>(c, B, s); break;
-    default: launch_bubble_d<3>(c, B, s); break;
+    case 1: launch_bubble_d<1>(c, B, mode, s); break;
+    case 2: launch_bubble_d<2>(c, B, mode, s); break;
+    default: launch_bubble_d<3>(c, B, mode, s); break;
     }
     prof_end(c, pr, s);
     return hipGetLastError() == hipSuccess ? BUB_OK : BUB_EHIP;
@@ -442,9 +467,10 @@ bool stage_fusable(const bub_ctx *c)
 {
     // (a viscous or source pass after the stage changes the state the epilogue would describe)
     if (!c->d_P2 || slots_for(c->N) != 1 || c->opts.viscous || c->src_on || ct_of(c) == CT_POLY) return false;
-    // 3D FP64: the epilogue's registers cost the stage more than the pass it saves (measured at 256^3
-    // x 21 bins: 13.6 ms fused against 11.9 + 1.5 ms)
-    if (c->ndim == 3 && c->opts.precision == BUB_PREC_FP64) return false;
+    // 3D FP64: the epilogue pays in the balanced-tile kernel of polytropic air (256^3 x 21 split: 42.3 against
+    // 44.0 ms a step); in the older kernel its registers cost the stage more than the pass it saves (13.6 ms
+    // against 11.9 + 1.5 ms)
+    if (c->ndim == 3 && c->opts.precision == BUB_PREC_FP64 && !(pw_fast(c) && tile_ok(c, kernel_shape(c)))) return false;
     int groups = 0, nt;
     if (uses_line(c)) line_grouping(c, &nt, &groups);
     else bin_grouping(c, stage_tiles(c), &groups);
@@ -835,7 +861,9 @@ int bub_rhs_stage(bub_ctx *c, const double *q, double *rhs, void *stream)
 
 namespace {
 
-// nsteps SSP-RK3 steps (Sec. 3).  With the fused epilogue (stage_fusable), stages 1 and 2 write the
+// nsteps SSP-RK3 steps (Sec. 3).  In split mode the bubble half-steps make the primitive pass of the state they
+// leave (bubble_prims): the first one for the flux part, the closing one of every step but the last for the next
+// step, with its wave-speed maxima.  With the fused epilogue (stage_fusable), stages 1 and 2 write the
 // primitives of the state they produce (P -> P2 -> P), so only the step's first stage needs a
 // primitive pass; in unsplit mode stage 3 of every step but the last also writes the primitives and
 // the wave-speed maxima of u^{n+1}, so the next step needs none.  Results are bitwise those of the
@@ -848,19 +876,22 @@ int rk3_steps_impl(bub_ctx *c, double *q, double *work, int nsteps, double dt, d
     const bool cfl = !(dt > 0.0);
     const bool fuse = stage_fusable(c);
     const bool carry = fuse && !split;   // the last bubble half-step of split mode changes u^{n+1}
+    const bool bprim = split && bubble_prims(c);
     double *Pa = c->d_P, *Pb = c->d_P2;  // Pa: primitives of the step's starting state
     int rc = BUB_OK;
     for (int k = 0; k < nsteps; ++k) {
         const bool more = k + 1 < nsteps;
-        if ((k == 0 || !carry) && (rc = prim(c, q, Pa, cfl ? PRIM_CFL : PRIM_ONLY, s))) return rc;
+        if ((k == 0 || !(carry || bprim)) && (rc = prim(c, q, Pa, cfl ? PRIM_CFL : PRIM_ONLY, s))) return rc;
         long pr = prof_begin(c, BUB_K_OTHER, s);
         hipLaunchKernelGGL(k_dt, dim3(1), dim3(WMAX_SLOTS), 0, s, c->d_sc, cfl ? 0.0 : dt, c->opts.cfl, dt_dev);
         prof_end(c, pr, s);
         HIP_OK(hipGetLastError());
         if (split) {
             // S_b(dt/2) first; the flux part then starts from the primitives of the advanced state
-            if ((rc = bubble(c, q, &c->d_sc->dt, 0.5, 0.0, c->nsub_diag, s))) return rc;
-            if ((rc = prim(c, q, Pa, PRIM_ONLY, s))) return rc;
+            if ((rc = bubble(c, q, &c->d_sc->dt, 0.5, 0.0, c->nsub_diag, bprim ? Pa : nullptr, PRIM_ONLY,
+                             Pa + (size_t)(c->ndim + 3) * c->N, s)))
+                return rc;
+            if (!bprim && (rc = prim(c, q, Pa, PRIM_ONLY, s))) return rc;
         }
         StageArgs A{};
         A.dtp = &c->d_sc->dt;
@@ -887,7 +918,8 @@ int rk3_steps_impl(bub_ctx *c, double *q, double *work, int nsteps, double dt, d
         if ((rc = stage(c, A, s, 0.5))) return rc;
         if (split &&   // S_b(dt/2)
             (rc = bubble(c, q, &c->d_sc->dt, 0.5, 0.0,
-                         c->nsub_diag ? c->nsub_diag + (size_t)c->nb * c->N : nullptr, s)))
+                         c->nsub_diag ? c->nsub_diag + (size_t)c->nb * c->N : nullptr, bprim && more ? Pa : nullptr,
+                         cfl ? PRIM_CFL : PRIM_ONLY, nullptr, s)))
             return rc;
         if (carry && more) std::swap(Pa, Pb);
     }
@@ -1136,7 +1168,7 @@ int bub_lagrangian_steps(bub_ctx *c, double *ql, double *bubbles, int64_t nbub, 
 int bub_bubble_advance(bub_ctx *c, double *q, double tau, int32_t *nsub, void *stream)
 {
     if (!c || !q || !(tau > 0.0) || tau == INFINITY) return BUB_EINVAL;
-    return bubble(c, q, nullptr, 0.0, tau, nsub, (hipStream_t)stream);
+    return bubble(c, q, nullptr, 0.0, tau, nsub, nullptr, BUBBLE_ONLY, nullptr, (hipStream_t)stream);
 }
 
 int bub_last_error(bub_ctx *c, int *code, int64_t *cell, int *bin, void *stream)

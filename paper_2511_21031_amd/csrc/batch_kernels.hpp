@@ -93,7 +93,7 @@ __global__ void __launch_bounds__(S * CELLS) k_bubble_group(const BatchMember *_
     A.tau_scale = 0.5;
     A.rtol = m.rtol;
     A.max_substeps = m.max_substeps;
-    bubble_block<D, S, CELLS, CT_FIFTHS>(A, m.g, m.ph, m.bt, m.sc, blockIdx.x - L->start[j]);
+    bubble_block<D, S, CELLS, CT_FIFTHS, BUBBLE_ONLY>(A, m.g, m.ph, m.bt, m.sc, blockIdx.x - L->start[j]);
 }
 
 // RK stage k (1, 2 or 3) of every listed member; list offsets count stage items.  Blocks are mapped

@@ -11,8 +11,11 @@
 #pragma once
 
 #include "device_common.hpp"
+#include "ee_kernels.hpp"
 
 namespace bub {
+
+constexpr int BUBBLE_ONLY = -1;   // bubble_block without a primitive pass
 
 struct BubbleArgs {
     double *q;
@@ -22,22 +25,34 @@ struct BubbleArgs {
     double rtol;
     int max_substeps;
     int *nsub;            // [nb][N] accepted sub-steps, or null
+    double *Pout;         // with a primitive pass: the primitive scratch of the advanced state
+    const double *n;      // the bubble number density of the state (the primitive scratch's row), or null: it is
+                          // summed up from the bins, a second reading of every n R
 };
 
 
-// Step-size factor 0.9 (rtol/err)^(1/3) of the embedded pair, without the FP64 library power (about a
-// hundred instructions, a third of an attempt's work).  The ratio is first held in [0.01, 100], which
-// changes no result: outside [0.0214, 87.8] the factor leaves [1/4, 4] and the caller's clamp takes the
-// limit either way.  Then z = x^(-1/3) from the FP32 hardware log2 and exp2 and two Newton steps on
-// x z^3 = 1, z <- z (4 - x z^3) / 3 (quadratic, no division), and x^(1/3) = x z^2, to a few ulp of the
-// library power, so attempts are sized as the oracle sizes them.
-__device__ __forceinline__ double step_factor3(double rtol, double err)
+// Step-size factor 0.9 x^(1/3), x = rtol/err, of the embedded pair, without the FP64 library power (about a
+// hundred instructions, a third of an attempt's work).  x is first held in [0.01, 100], which changes no
+// result: outside [0.0214, 87.8] the factor leaves [1/4, 4] and the caller's clamp takes the limit either
+// way.  Then z = x^(-1/3) from the FP32 hardware log2 and exp2 and two Newton steps on x z^3 = 1,
+// z <- z (4 - x z^3) / 3 (quadratic, no division), and x^(1/3) = x z^2, to a few ulp of the library power,
+// so attempts are sized as the oracle sizes them.
+__device__ __forceinline__ double step_factor3(double x)
 {
-    const double x = dmin(100.0, dmax(0.01, rtol / err));
+    x = dmin(100.0, dmax(0.01, x));
     double z = (double)__builtin_amdgcn_exp2f((-1.0f / 3.0f) * __builtin_amdgcn_logf((float)x));
 #pragma unroll
     for (int k = 0; k < 2; ++k) z = (z * (1.0 / 3.0)) * fma(-x, z * z * z, 4.0);
     return 0.9 * (x * z * z);
+}
+
+// rtol / (|d| / scale) of one component of the error norm: an attempt is accepted when the smallest is at
+// least 1, and that smallest is the step-size factor's argument, so an attempt takes one reciprocal per
+// component where the norm and its inverse took a division each and one more.
+__device__ __forceinline__ double err_ratio(double rtol, double d, double scale)
+{
+    const double a = fabs(d);
+    return rtol * scale * frcp(a < 1e-290 ? 1e-290 : a);   // (NaN stays NaN)
 }
 
 // Adaptive integration of one bin over tau: (y0, y1) = (R, Rdot) in, advanced values out.
@@ -64,18 +79,16 @@ __device__ inline int bubble_bin(const Phys &ph, double &y0, double &y1, double 
         double k3r = b1, k3v = km_rddot<PW>(ph, b0, b1, r0, pg0, pl, irhol, ic);
         double n0 = y0 * (1.0 / 3.0) + (2.0 / 3.0) * (b0 + h * k3r);
         double n1 = y1 * (1.0 / 3.0) + (2.0 / 3.0) * (b1 + h * k3v);
-        double err = dmax(fabs(n0 - e0) / fabs(n0), fabs(n1 - e1) / dmax(fabs(n1), vfloor));
-        if (!(err == err)) err = INFINITY;
-        if (err <= rtol && n0 > 0.0) {
+        const double xr = err_ratio(rtol, n0 - e0, fabs(n0)), xv = err_ratio(rtol, n1 - e1, dmax(fabs(n1), vfloor));
+        const bool ok = xr >= 1.0 && xv >= 1.0 && n0 > 0.0;   // (false for NaN)
+        if (ok) {
             t += h;
             y0 = n0;
             y1 = n1;
             ++accepted;
+            if (!(t < tau)) break;   // most bins take one sub-step: no next one to size
         }
-        double fac = err > 0.0 ? step_factor3(rtol, err) : 4.0;
-        if (!(n0 > 0.0)) fac = 0.25;
-        fac = dmin(4.0, dmax(0.25, fac));
-        h *= fac;
+        h *= xr == xr && xv == xv && n0 > 0.0 ? dmin(4.0, dmax(0.25, step_factor3(dmin(xr, xv)))) : 0.25;
     }
     return accepted;
 }
@@ -119,21 +132,20 @@ __device__ inline int bubble_bin_tr(const Phys &ph, double *y, double mg, double
         tr_rates(ph, mg, pl, irhol, ic, b, k3);
 #pragma unroll
         for (int j = 0; j < 4; ++j) nn[j] = y[j] * (1.0 / 3.0) + (2.0 / 3.0) * (b[j] + h * k3[j]);
-        double err = dmax(fabs(nn[0] - e[0]) / fabs(nn[0]), fabs(nn[1] - e[1]) / dmax(fabs(nn[1]), vfloor));
-        err = dmax(err, fabs(nn[2] - e[2]) / fabs(nn[2]));
-        err = dmax(err, fabs(nn[3] - e[3]) / (fabs(nn[3]) + mg));
-        if (!(err == err)) err = INFINITY;
+        const double xr = err_ratio(rtol, nn[0] - e[0], fabs(nn[0]));
+        const double xv = err_ratio(rtol, nn[1] - e[1], dmax(fabs(nn[1]), vfloor));
+        const double xp = err_ratio(rtol, nn[2] - e[2], fabs(nn[2]));
+        const double xm = err_ratio(rtol, nn[3] - e[3], fabs(nn[3]) + mg);
         const bool pos = nn[0] > 0.0 && nn[2] > 0.0;
-        if (err <= rtol && pos) {
+        if (xr >= 1.0 && xv >= 1.0 && xp >= 1.0 && xm >= 1.0 && pos) {   // (false for NaN)
             t += h;
 #pragma unroll
             for (int j = 0; j < 4; ++j) y[j] = nn[j];
             ++accepted;
+            if (!(t < tau)) break;
         }
-        double fac = err > 0.0 ? step_factor3(rtol, err) : 4.0;
-        if (!pos) fac = 0.25;
-        fac = dmin(4.0, dmax(0.25, fac));
-        h *= fac;
+        const bool num = xr == xr && xv == xv && xp == xp && xm == xm;
+        h *= num && pos ? dmin(4.0, dmax(0.25, step_factor3(dmin(dmin(xr, xv), dmin(xp, xm))))) : 0.25;
     }
     return accepted;
 }
@@ -143,8 +155,14 @@ __device__ inline int bubble_bin_tr(const Phys &ph, double *y, double mg, double
 // slots first pool sum w (nR)^3 for n (one barrier), then each advances its bins, posts its part
 // of sum w R^3 before and after, and bumps the cell's LDS counter; the slot that arrives last
 // updates alpha, so waves whose bins need fewer sub-steps leave without waiting.
+// MODE (PRIM_ONLY, PRIM_CFL): the half-step also makes the primitive pass of the state it leaves (the arithmetic and
+// the order of k_prim, so the same bits): the bins' sums are added up as they are stored and the thread that
+// finishes a cell writes its primitives, which saves that pass's reading of every bin.  256^3 x 21
+// FP64, with n from the primitives at hand and reciprocals for divisions in the error norm: a split step 50.4 to
+// 46.7 ms; 2000 x 31 in 1D 68 to 59 us.
+// BUBBLE_ONLY: no primitives.
 // Block `blk` of the half-step (cells blk*CELLS ..); every thread of the workgroup calls it.
-template <int D, int S, int CELLS, int CT>
+template <int D, int S, int CELLS, int CT, int MODE>
 __device__ __forceinline__ void bubble_block(const BubbleArgs &A, const Grid &g, const Phys &ph, const Bins &bins,
                                              Scalars *sc, long long blk)
 {
@@ -173,9 +191,13 @@ __device__ __forceinline__ void bubble_block(const BubbleArgs &A, const Grid &g,
         ic = frcp(sqrt(ph.gamma * (pl + ph.pi_inf) * irhol));
     }
     const bool act = live && a > 0.0;
+    constexpr bool PRIM = MODE != BUBBLE_ONLY;
+    [[maybe_unused]] BinSums ps;
+    ps.bad = nb;
+    [[maybe_unused]] double wmax = 0.0;
     // n from sum w (nR)^3
     double s3 = 0.0;
-    if (act)
+    if (act && !A.n)
         for (int i = slot; i < nb; i += S) {
             double x = q[(iNR + i) * N + c];
             s3 += bins.w[i] * (x * x * x);
@@ -200,7 +222,7 @@ __device__ __forceinline__ void bubble_block(const BubbleArgs &A, const Grid &g,
     const double vfloor = 1e-3 * sqrt(ph.p0 / ph.rho0);
     double m3_old = 0.0, m3_new = 0.0;
     if (act) {
-        const double n = sqrt(FOUR_PI_3 * s3 / a);
+        const double n = A.n ? A.n[c] : sqrt(FOUR_PI_3 * s3 / a);
         const double in = frcp(n);
         for (int i = slot; i < nb; i += S) {
             double y0 = q[(iNR + i) * N + c] * in;
@@ -216,9 +238,11 @@ __device__ __forceinline__ void bubble_block(const BubbleArgs &A, const Grid &g,
                 y1 = y[1];
                 q[(iNP + i) * N + c] = n * y[2];
                 q[(iNM + i) * N + c] = n * y[3];
+                if constexpr (PRIM) bin_add_tr(ps, i, n * y0, n * y1, n * y[2], wi, nb);
             } else {
                 acc = bubble_bin<pw_of(CT)>(ph, y0, y1, bins.r0[i], bins.pg0[i], pl, irhol, ic, tau, A.rtol,
                                                   vfloor, A.max_substeps, sc, c, i);
+                if constexpr (PRIM) bin_add<pw_of(CT)>(ps, i, n * y0, n * y1, wi, bins.pg0[i], bins.r0[i], nb, ph, nullptr);
             }
             q[(iNR + i) * N + c] = n * y0;
             q[(iNV + i) * N + c] = n * y1;
@@ -230,28 +254,60 @@ __device__ __forceinline__ void bubble_block(const BubbleArgs &A, const Grid &g,
     }
     if constexpr (S == 1) {
         if (act) q[iA * N + c] = a * m3_new / m3_old;   // alpha = (4 pi/3) n mean(R^3) at fixed n
+        if constexpr (PRIM) {
+            if (live) wmax = prim_finish<D, MODE, CT>(q, A.Pout, g, ph, bins, sc, c, ps);
+        }
     } else {
         s_a[slot * CELLS + cl] = m3_old;
         s_b[slot * CELLS + cl] = m3_new;
+        [[maybe_unused]] double *s_sum = nullptr;
+        [[maybe_unused]] int *s_bad = nullptr;
+        if constexpr (PRIM) {
+            __shared__ double s_ps[5][S][CELLS];
+            __shared__ int s_pbad[S][CELLS];
+            s_sum = &s_ps[0][0][0];
+            s_bad = &s_pbad[0][0];
+            const double v[5] = {ps.s3, ps.s2, ps.s21, ps.s32, ps.sp};
+#pragma unroll
+            for (int k = 0; k < 5; ++k) s_sum[(k * S + slot) * CELLS + cl] = v[k];
+            s_bad[slot * CELLS + cl] = ps.bad;
+        }
         __threadfence_block();
         const unsigned arrived = atomicAdd(&s_cnt[cl], 1u);
-        if (arrived == S - 1 && act) {
+        if (arrived == S - 1 && (PRIM ? live : act)) {
             __threadfence_block();
-            double mo = 0.0, mn = 0.0;
+            if (act) {
+                double mo = 0.0, mn = 0.0;
 #pragma unroll
-            for (int k = 0; k < S; ++k) {
-                mo += s_a[k * CELLS + cl];
-                mn += s_b[k * CELLS + cl];
+                for (int k = 0; k < S; ++k) {
+                    mo += s_a[k * CELLS + cl];
+                    mn += s_b[k * CELLS + cl];
+                }
+                q[iA * N + c] = a * mn / mo;
             }
-            q[iA * N + c] = a * mn / mo;
+            if constexpr (PRIM) {
+                BinSums t;
+                t.bad = nb;
+#pragma unroll
+                for (int k = 0; k < S; ++k) {
+                    t.s3 += s_sum[(0 * S + k) * CELLS + cl];
+                    t.s2 += s_sum[(1 * S + k) * CELLS + cl];
+                    t.s21 += s_sum[(2 * S + k) * CELLS + cl];
+                    t.s32 += s_sum[(3 * S + k) * CELLS + cl];
+                    t.sp += s_sum[(4 * S + k) * CELLS + cl];
+                    t.bad = s_bad[k * CELLS + cl] < t.bad ? s_bad[k * CELLS + cl] : t.bad;
+                }
+                wmax = prim_finish<D, MODE, CT>(q, A.Pout, g, ph, bins, sc, c, t);
+            }
         }
     }
+    if constexpr (MODE == PRIM_CFL) cfl_reduce(wmax, sc);
 }
 
-template <int D, int S, int CELLS, int CT>
+template <int D, int S, int CELLS, int CT, int MODE>
 __global__ void __launch_bounds__(S * CELLS) k_bubble(BubbleArgs A, Grid g, Phys ph, Bins bins, Scalars *sc)
 {
-    bubble_block<D, S, CELLS, CT>(A, g, ph, bins, sc, blockIdx.x);
+    bubble_block<D, S, CELLS, CT, MODE>(A, g, ph, bins, sc, blockIdx.x);
 }
 
 }  // namespace bub

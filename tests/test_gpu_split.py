@@ -168,3 +168,27 @@ def test_split_trajectory_1d_2d_requests(torch, bub, orc, kind):
     case = _serving_requests()[kind]
     pb, got, q_ref, diverged = _split_trajectory(torch, bub, orc, case, 6)
     _judge_split(orc, pb, got, q_ref, diverged, f"split {kind} {case.n} nb {case.nb}, 6 steps")
+
+
+@pytest.mark.parametrize("contents", [False, True])
+@pytest.mark.parametrize("n", [(130,), (300, 260), (520, 515), (84, 84, 84)])
+def test_steps_in_one_call_are_single_steps(n, contents):
+    """Split mode: a call of several steps takes the next step's primitives and wave speeds from the closing bubble
+    half-step, single steps from the primitive pass: the same bits, with one to eight threads per cell."""
+    import dataclasses
+
+    import torch
+    import paper_2511_21031_amd as bub
+    case = W.random_smooth(len(n), n, 1e-4, 3, seed=51, bc=1, amp_atm=2.0)
+    if contents:
+        case = dataclasses.replace(case, gas=dict(W.AIR_WITH_VAPOUR), contents=dict(W.AIR_VAPOUR))
+    outs = []
+    for calls in ((3,), (1, 1, 1)):
+        ctx = bub.context_from_case(case, bubble_mode=bub.BUBBLES_SPLIT)
+        q = ctx.init_state(torch.from_numpy(case.prim).cuda())
+        work = ctx.new_work()
+        for k in calls:
+            ctx.rk3_steps(q, work, k)
+        assert ctx.last_error()[0] == 0
+        outs.append(q)
+    assert torch.equal(outs[0], outs[1])
