@@ -112,29 +112,37 @@ __device__ inline void el_support(const double *b, long long nb, long long i, co
 // bubble's wavefront take the (x, y) points of the (2m+1)^2 stencil plane (more passes when it exceeds 64)
 // and each walks the 2m+1 z planes of its column, so no lane divides by the stencil width per cell.
 // f(c, e) for every cell c inside the domain and the cut-off, e = exp(-d^2 / (2 h^2)) (the Gaussian
-// without its normalisation).
+// without its normalisation), as the column's factor times the plane's: one exponential per column and, on
+// the plane's own lane, one per plane (handed round by readlane, 64 planes at a time) in place of one per cell:
+// the gather of 1e5 bubbles 0.130 -> 0.118 ms.
 template <typename F>
 __device__ __forceinline__ void el_visit(const ElGrid &g, const int host[3], const double xb[3], double h, int m,
                                          int lane, F &&f)
 {
-    const int w = 2 * m + 1, w2 = w * w;
+    const int w = __builtin_amdgcn_readfirstlane(2 * m + 1), w2 = w * w;
     const double cut = 9.0 * h * h, nh = -0.5 / (h * h);
     const long long nxy = (long long)g.n[0] * g.n[1];
-    for (int p = lane; p < w2; p += 64) {
-        const int ix = host[0] + p % w - m, iy = host[1] + p / w - m;
-        const int cx = el_wrap(ix, g.n[0], g.bc[0]), cy = el_wrap(iy, g.n[1], g.bc[1]);
-        if (cx < 0 || cy < 0) continue;
-        const double ex = (ix + 0.5) * g.dx - xb[0], ey = (iy + 0.5) * g.dx - xb[1];
-        const double dxy = ex * ex + ey * ey;
-        if (!(dxy < cut)) continue;
-        const long long cxy = cx + (long long)g.n[0] * cy;
-        for (int iz = host[2] - m; iz <= host[2] + m; ++iz) {
-            const int cz = el_wrap(iz, g.n[2], g.bc[2]);
-            if (cz < 0) continue;
-            const double ez = (iz + 0.5) * g.dx - xb[2];
-            const double d2 = dxy + ez * ez;
-            if (!(d2 < cut)) continue;
-            f(cxy + nxy * cz, exp(d2 * nh));
+    for (int z0 = 0; z0 < w; z0 += 64) {
+        const double zl = (host[2] - m + z0 + lane + 0.5) * g.dx - xb[2], zf = exp(zl * zl * nh);
+        const int zlo = __double2loint(zf), zhi = __double2hiint(zf), nz = w - z0 < 64 ? w - z0 : 64;
+        for (int p = lane; p < w2; p += 64) {
+            const int ix = host[0] + p % w - m, iy = host[1] + p / w - m;
+            const int cx = el_wrap(ix, g.n[0], g.bc[0]), cy = el_wrap(iy, g.n[1], g.bc[1]);
+            if (cx < 0 || cy < 0) continue;
+            const double ex = (ix + 0.5) * g.dx - xb[0], ey = (iy + 0.5) * g.dx - xb[1];
+            const double dxy = ex * ex + ey * ey;
+            if (!(dxy < cut)) continue;
+            const double exy = exp(dxy * nh);
+            const long long cxy = cx + (long long)g.n[0] * cy;
+            for (int k = 0; k < nz; ++k) {
+                const int iz = host[2] - m + z0 + k;
+                const int cz = el_wrap(iz, g.n[2], g.bc[2]);
+                if (cz < 0) continue;
+                const double ez = (iz + 0.5) * g.dx - xb[2];
+                const double d2 = dxy + ez * ez;
+                if (!(d2 < cut)) continue;
+                f(cxy + nxy * cz, exy * __hiloint2double(__builtin_amdgcn_readlane(zhi, k), __builtin_amdgcn_readlane(zlo, k)));
+            }
         }
     }
 }
@@ -327,27 +335,24 @@ __device__ inline void el_face_flux(const double (&st)[6][5], const Phys &ph, do
             WR[v] = st[3][v];
         }
     }
-    double EK[2], cK[2];
-    const double *Ws[2] = {WL, WR};
-    for (int s = 0; s < 2; ++s) {
-        const double *W = Ws[s];
-        EK[s] = (W[4] + ph.gpi) * ph.inv_gm1 + 0.5 * W[0] * (W[1] * W[1] + W[2] * W[2] + W[3] * W[3]);
-        cK[s] = sqrt(ph.gamma * (W[4] + ph.pi_inf) / W[0]);
-    }
-    double ul = WL[1 + d], ur = WR[1 + d];
-    double SL = dmin(ul - cK[0], ur - cK[1]), SR = dmax(ul + cK[0], ur + cK[1]);
-    double mL = WL[0] * (SL - ul), mR = WR[0] * (SR - ur);
-    double Ss = (WR[4] - WL[4] + ul * mL - ur * mR) / (mL - mR);
-    int side, star;
-    if (SL >= 0.0) { side = 0; star = 0; }
-    else if (Ss >= 0.0) { side = 0; star = 1; }
-    else if (SR > 0.0) { side = 1; star = 1; }
-    else { side = 1; star = 0; }
-    const double *W = side ? WR : WL;
-    double SK = side ? SR : SL, un = W[1 + d], ek = EK[side], pk = W[4], rk = W[0];
-    double fac = star ? SK * (Ss - un) / (SK - Ss) : 0.0;
-    F[0] = rk * un + fac * rk;
-    for (int e = 0; e < 3; ++e) F[1 + e] = rk * un * W[1 + e] + (e == d ? pk : 0.0) + fac * rk * (e == d ? SK : W[1 + e]);
+    // sound speeds: sqrt(x / rho) = x / sqrt(x rho), one reciprocal root and no division
+    const double xL = ph.gamma * (WL[4] + ph.pi_inf), xR = ph.gamma * (WR[4] + ph.pi_inf);
+    const double cL = xL * frsqrt(xL * WL[0]), cR = xR * frsqrt(xR * WR[0]);
+    const double ul = WL[1 + d], ur = WR[1 + d];
+    const double SL = dmin(ul - cL, ur - cR), SR = dmax(ul + cL, ur + cR);
+    const double mL = WL[0] * (SL - ul), mR = WR[0] * (SR - ur);
+    const double Ss = (WR[4] - WL[4] + ul * mL - ur * mR) * frcp(mL - mR);
+    const bool right = !(SL >= 0.0) && !(Ss >= 0.0), star = !(SL >= 0.0) && (Ss >= 0.0 || SR > 0.0);
+    double W[5];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) W[v] = right ? WR[v] : WL[v];
+    const double SK = right ? SR : SL, un = W[1 + d], pk = W[4], rk = W[0];
+    const double ek = (pk + ph.gpi) * ph.inv_gm1 + 0.5 * rk * (W[1] * W[1] + W[2] * W[2] + W[3] * W[3]);
+    const double fac = star ? SK * (Ss - un) * frcp(SK - Ss) : 0.0;
+    const double ru = rk * un, fr = fac * rk;
+    F[0] = ru + fr;
+#pragma unroll
+    for (int e = 0; e < 3; ++e) F[1 + e] = e == d ? ru * un + pk + fr * SK : F[0] * W[1 + e];
     F[4] = (ek + pk) * un + fac * (ek + pk + rk * Ss * (SK - un));
     pL = WL[4];
     pR = WR[4];
@@ -360,6 +365,12 @@ __device__ inline void el_face_flux(const double (&st)[6][5], const Phys &ph, do
 // each direction the tile's cells and their 3-cell halos along it are first staged in LDS as a "line"
 // array (extent T_d + 6 along d), so every face reads its six-cell stencil there at a constant stride;
 // mirrored ghosts are stored with the normal velocity negated.
+// Bound by FP64 vector instructions (active 72% of the time; 1830 a wavefront) and the waits around four
+// barriers a direction, so it wants wavefronts: with the faces laid over the line array that they came from,
+// 23 KB a workgroup instead of 37, a SIMD holds five instead of four.  192^3 cells: 0.90 ms with a
+// separate face array, IEEE divisions and the ghost map for every tile; 0.78 without the last two; 0.72 now
+// (the 1.5 GB that a stage has to move take 0.32 ms).  6x6x6 cells (84% of the threads own a cell,
+// 75% here) take 0.73, 8x8x7 with 512 threads 0.82, 8x8x5 with 384 0.95: fewer, larger barriers.
 constexpr int ELT_X = 8, ELT_Y = 8, ELT_Z = 3, ELT_BLOCK = 256;
 
 // Index in the line array of direction d of local cell (i, j, k), coordinate d in [-3, T_d + 3).
@@ -375,12 +386,12 @@ __global__ void __launch_bounds__(ELT_BLOCK) k_el_stage(ElStageArgs A, ElGrid g,
                                                         int per_xcd)
 {
     constexpr int TX = ELT_X, TY = ELT_Y, TZ = ELT_Z, T = TX * TY * TZ;
-    constexpr int FMAX = TX * TY * (TZ + 1) > (TX + 1) * TY * TZ ? TX * TY * (TZ + 1) : (TX + 1) * TY * TZ;
-    constexpr int LMAX = TX * TY * (TZ + 6) > (TX + 6) * TY * TZ ? TX * TY * (TZ + 6) : (TX + 6) * TY * TZ;
-    // per face: flux[5], the face pressure (p_L + p_R)/2 and (p_L u_L + p_R u_R)/2; with the line
-    // array 37 KB, so four workgroups (16 waves) fit a CU's LDS
-    __shared__ double s_f[7][FMAX];
-    __shared__ double s_l[5][LMAX];    // line array of the current direction: rho, u, v, w, p
+    constexpr int LX = (TX + 6) * TY * TZ, LY = TX * (TY + 6) * TZ, LZ = TX * TY * (TZ + 6);
+    constexpr int LMAX = LX > LY ? (LX > LZ ? LX : LZ) : (LY > LZ ? LY : LZ);
+    // the line array of the current direction (rho, u, v, w, p) and, once every thread has its face in registers,
+    // in the same place per face: flux[5], the pressure (p_L + p_R)/2 and (p_L u_L + p_R u_R)/2
+    __shared__ double s_l[5][LMAX];
+    double *const s_f = &s_l[0][0];
     const long long N = g.N;
     const int tid = threadIdx.x;
     // XCD-aware order: blocks are dealt round-robin over the 8 XCDs, so block b takes tile
@@ -398,9 +409,23 @@ __global__ void __launch_bounds__(ELT_BLOCK) k_el_stage(ElStageArgs A, ElGrid g,
         constexpr int d = decltype(dtag)::value;
         constexpr int EX = TX + 6 * (d == 0), EY = TY + 6 * (d == 1), EZ = TZ + 6 * (d == 2), LD = EX * EY * EZ;
         constexpr int STRIDE = d == 0 ? 1 : (d == 1 ? TX : TX * TY);
-        // stage the tile and its halos along d (every coordinate through the ghost map; only the
-        // mirror along d flips a velocity, the only one the faces of d read across a wall)
-        for (int e = tid; e < LD; e += ELT_BLOCK) {
+        // stage the tile and its halos along d: a tile whose lines lie inside the grid needs no ghost map (the
+        // test is the workgroup's), and byte offsets of 32 bits reach its cells where the grid has fewer than
+        // 2^29; else every coordinate goes through the map, and only the mirror along d flips a velocity, the
+        // only one the faces of d read across a wall
+        if (N < (1ll << 29) && x0 >= 3 && y0 >= 3 && z0 >= 3 && x0 + TX + 3 <= g.n[0] && y0 + TY + 3 <= g.n[1] && z0 + TZ + 3 <= g.n[2]) {
+            const unsigned base = 8u * (unsigned)(x0 + g.n[0] * (y0 + g.n[1] * z0));
+#pragma unroll
+            for (int r = 0; r < (LD + ELT_BLOCK - 1) / ELT_BLOCK; ++r) {
+                const int e = tid + r * ELT_BLOCK;
+                if (e < LD) {
+                    const int i = e % EX - 3 * (d == 0), j = (e / EX) % EY - 3 * (d == 1), k = e / (EX * EY) - 3 * (d == 2);
+                    const unsigned off = base + 8u * (unsigned)(i + g.n[0] * (j + g.n[1] * k));
+#pragma unroll
+                    for (int v = 0; v < 5; ++v) s_l[v][e] = *(const double *)((const char *)(A.P + v * N) + off);
+                }
+            }
+        } else for (int e = tid; e < LD; e += ELT_BLOCK) {
             const int i = e % EX - 3 * (d == 0), j = (e / EX) % EY - 3 * (d == 1), k = e / (EX * EY) - 3 * (d == 2);
             bool fl[3] = {false, false, false};
             const int gx = map_coord(x0 + i, g.n[0], g.bc[0], fl[0]);
@@ -413,34 +438,38 @@ __global__ void __launch_bounds__(ELT_BLOCK) k_el_stage(ElStageArgs A, ElGrid g,
             if (fl[d]) s_l[1 + d][li_] = -s_l[1 + d][li_];
         }
         __syncthreads();
+        // a face per thread; faces of cells outside the grid are not needed (the face at n[d] closes the last cell)
         constexpr int BX = TX + (d == 0), BY = TY + (d == 1), BZ = TZ + (d == 2), FD = BX * BY * BZ;
-        for (int t = tid; t < FD; t += ELT_BLOCK) {
-            const int fi = t % BX, fj = (t / BX) % BY, fk = t / (BX * BY);
-            const int f[3] = {x0 + fi, y0 + fj, z0 + fk};
-            // faces of cells outside the grid are not needed (the face at n[d] closes the last cell)
-            bool need = true;
-            for (int e = 0; e < 3; ++e) need = need && (e == d ? f[e] <= g.n[e] : f[e] < g.n[e]);
-            if (!need) continue;
+        static_assert(FD <= ELT_BLOCK && 7 * FD <= 5 * LMAX, "faces");
+        const int fi = tid % BX, fj = (tid / BX) % BY, fk = tid / (BX * BY);
+        const bool need = tid < FD && x0 + fi < g.n[0] + (d == 0) && y0 + fj < g.n[1] + (d == 1) && z0 + fk < g.n[2] + (d == 2);
+        double F[5] = {0, 0, 0, 0, 0}, pf = 0.0, puf = 0.0;
+        if (need) {
             const int b0 = el_lidx<d>(fi - 3 * (d == 0), fj - 3 * (d == 1), fk - 3 * (d == 2));
             double st[6][5];
 #pragma unroll
             for (int o = 0; o < 6; ++o)
 #pragma unroll
                 for (int v = 0; v < 5; ++v) st[o][v] = s_l[v][b0 + o * STRIDE];
-            double F[5], pl, pr, ul, ur;
+            double pl, pr, ul, ur;
             el_face_flux<d>(st, ph, F, pl, pr, ul, ur);
-            for (int k = 0; k < 5; ++k) s_f[k][t] = F[k];
-            s_f[5][t] = 0.5 * (pl + pr);
-            s_f[6][t] = 0.5 * (pl * ul + pr * ur);
+            pf = 0.5 * (pl + pr);
+            puf = 0.5 * (pl * ul + pr * ur);
+        }
+        __syncthreads();
+        if (need) {
+            for (int k = 0; k < 5; ++k) s_f[k * FD + tid] = F[k];
+            s_f[5 * FD + tid] = pf;
+            s_f[6 * FD + tid] = puf;
         }
         __syncthreads();
         if (active) {
             const int lo = li + BX * (lj + BY * lk);
             const int hi = lo + (d == 0 ? 1 : (d == 1 ? BX : BX * BY));
 #pragma unroll
-            for (int k = 0; k < 5; ++k) L[k] += (s_f[k][lo] - s_f[k][hi]) * g.inv_dx;
-            gradp[d] = (s_f[5][hi] - s_f[5][lo]) * g.inv_dx;
-            divpu += (s_f[6][hi] - s_f[6][lo]) * g.inv_dx;
+            for (int k = 0; k < 5; ++k) L[k] += (s_f[k * FD + lo] - s_f[k * FD + hi]) * g.inv_dx;
+            gradp[d] = (s_f[5 * FD + hi] - s_f[5 * FD + lo]) * g.inv_dx;
+            divpu += (s_f[6 * FD + hi] - s_f[6 * FD + lo]) * g.inv_dx;
         }
         __syncthreads();   // s_l and s_f are rewritten by the next direction
     };

@@ -87,3 +87,27 @@ BOX = [((8, 8, 3), 0), ((9, 9, 4), 1), ((7, 7, 2), 2), ((16, 8, 7), 1), ((17, 10
 @pytest.mark.parametrize("n,bc", PLANE + BOX)
 def test_balanced_tiles(torch, bub, orc, n, bc, contents):
     _check(torch, bub, orc, n, bc, contents, 5 if len(n) == 2 else 3, everywhere=bc != 0)
+
+
+@pytest.mark.parametrize("bc", [0, 1])
+@pytest.mark.parametrize("n", [(19, 22, 9), (30, 14, 13), (8, 25, 7)])
+def test_liquid_tiles_inside_the_grid(torch, bub, orc, bc, n):
+    """Liquid right-hand side of grids that have tiles away from every end (staged without the ghost map) next to
+    tiles that reach one, and of one that has none.  The bound is that of the other liquid right-hand sides: 1e-12
+    of the flux-divergence scale."""
+    rng = np.random.default_rng(5)
+    N, dx = int(np.prod(n)), 1e-4
+    prim = np.empty((5, N))
+    prim[0] = 1000.0 + 5.0 * rng.standard_normal(N)
+    prim[1:4] = 3.0 * rng.standard_normal((3, N))
+    prim[4] = 1e5 + 3e4 * rng.standard_normal(N)
+    alpha, rate = 0.01 * rng.random(N), 20.0 * rng.standard_normal(N)
+    pb = orc.problem(3, n, (dx,) * 3, ((bc, bc),) * 3, 1)
+    ctx = bub.Context(3, n, (dx,) * 3, ((bc, bc),) * 3, 1)
+    ql = orc.el_liquid_state(pb, prim)
+    ref = orc.el_rhs(pb, ql, alpha, rate)
+    got = ctx.lagrangian_rhs(torch.from_numpy(ql).cuda(), torch.from_numpy(np.vstack([alpha, rate])).cuda()).cpu().numpy()
+    scale = np.abs(ref).max(axis=1) + 1500.0 / dx * np.abs(ql).max(axis=1)
+    scale[1:4] += np.abs(prim[4]).max() / dx
+    err = np.abs(got - ref).max(axis=1) / scale
+    assert err.max() < 1e-12, err
