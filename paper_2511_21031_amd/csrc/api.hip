@@ -180,14 +180,14 @@ void launch_prim_p(bub_ctx *c, const double *q, double *out, int mode, hipStream
                            c->d_sc);
 }
 
-template <int D, int S, int CELLS>
+template <int D, int S>
 void launch_prim_s(bub_ctx *c, const double *q, double *out, int mode, hipStream_t s)
 {
     switch (ct_air(c)) {
-    case CT_AIR: launch_prim_p<D, S, CELLS, CT_AIR>(c, q, out, mode, s); break;
-    case CT_FIFTHS: launch_prim_p<D, S, CELLS, CT_FIFTHS>(c, q, out, mode, s); break;
-    case CT_TRANSFER: launch_prim_p<D, S, CELLS, CT_TRANSFER>(c, q, out, mode, s); break;
-    default: launch_prim_p<D, S, CELLS, CT_POLY>(c, q, out, mode, s); break;
+    case CT_AIR: launch_prim_p<D, S, slot_cells(S), CT_AIR>(c, q, out, mode, s); break;
+    case CT_FIFTHS: launch_prim_p<D, S, slot_cells(S), CT_FIFTHS>(c, q, out, mode, s); break;
+    case CT_TRANSFER: launch_prim_p<D, S, slot_cells(S), CT_TRANSFER>(c, q, out, mode, s); break;
+    default: launch_prim_p<D, S, slot_cells(S), CT_POLY>(c, q, out, mode, s); break;
     }
 }
 
@@ -195,11 +195,13 @@ template <int D>
 int launch_prim(bub_ctx *c, const double *q, double *out, int mode, hipStream_t s)
 {
     long pr = prof_begin(c, BUB_K_PRIM, s);
-    switch (slots_for(c->g.N)) {
-    case 1: launch_prim_s<D, 1, 256>(c, q, out, mode, s); break;
-    case 2: launch_prim_s<D, 2, 64>(c, q, out, mode, s); break;
-    case 4: launch_prim_s<D, 4, 64>(c, q, out, mode, s); break;
-    default: launch_prim_s<D, 8, 64>(c, q, out, mode, s); break;
+    switch (slots_for(c->g.N, c->nb)) {
+    case 1: launch_prim_s<D, 1>(c, q, out, mode, s); break;
+    case 2: launch_prim_s<D, 2>(c, q, out, mode, s); break;
+    case 4: launch_prim_s<D, 4>(c, q, out, mode, s); break;
+    case 8: launch_prim_s<D, 8>(c, q, out, mode, s); break;
+    case 16: launch_prim_s<D, 16>(c, q, out, mode, s); break;
+    default: launch_prim_s<D, 32>(c, q, out, mode, s); break;
     }
     prof_end(c, pr, s);
     return hipGetLastError() == hipSuccess ? BUB_OK : BUB_EHIP;
@@ -290,25 +292,27 @@ void launch_bubble_p(bub_ctx *c, const BubbleArgs &B, int mode, hipStream_t s)
     hipLaunchKernelGGL((k_bubble<D, S, CELLS, CT, BUBBLE_ONLY>), grid, block, 0, s, B, c->g, c->ph, c->bt, c->d_sc);
 }
 
-template <int D, int S, int CELLS>
+template <int D, int S>
 void launch_bubble_s(bub_ctx *c, const BubbleArgs &B, int mode, hipStream_t s)
 {
     switch (ct_air(c)) {
-    case CT_AIR: launch_bubble_p<D, S, CELLS, CT_AIR>(c, B, mode, s); break;
-    case CT_FIFTHS: launch_bubble_p<D, S, CELLS, CT_FIFTHS>(c, B, mode, s); break;
-    case CT_TRANSFER: launch_bubble_p<D, S, CELLS, CT_TRANSFER>(c, B, mode, s); break;
-    default: launch_bubble_p<D, S, CELLS, CT_POLY>(c, B, mode, s); break;
+    case CT_AIR: launch_bubble_p<D, S, slot_cells(S), CT_AIR>(c, B, mode, s); break;
+    case CT_FIFTHS: launch_bubble_p<D, S, slot_cells(S), CT_FIFTHS>(c, B, mode, s); break;
+    case CT_TRANSFER: launch_bubble_p<D, S, slot_cells(S), CT_TRANSFER>(c, B, mode, s); break;
+    default: launch_bubble_p<D, S, slot_cells(S), CT_POLY>(c, B, mode, s); break;
     }
 }
 
 template <int D>
 void launch_bubble_d(bub_ctx *c, const BubbleArgs &B, int mode, hipStream_t s)
 {
-    switch (slots_for(c->g.N)) {
-    case 1: launch_bubble_s<D, 1, 256>(c, B, mode, s); break;
-    case 2: launch_bubble_s<D, 2, 64>(c, B, mode, s); break;
-    case 4: launch_bubble_s<D, 4, 64>(c, B, mode, s); break;
-    default: launch_bubble_s<D, 8, 64>(c, B, mode, s); break;
+    switch (slots_for(c->g.N, c->nb)) {
+    case 1: launch_bubble_s<D, 1>(c, B, mode, s); break;
+    case 2: launch_bubble_s<D, 2>(c, B, mode, s); break;
+    case 4: launch_bubble_s<D, 4>(c, B, mode, s); break;
+    case 8: launch_bubble_s<D, 8>(c, B, mode, s); break;
+    case 16: launch_bubble_s<D, 16>(c, B, mode, s); break;
+    default: launch_bubble_s<D, 32>(c, B, mode, s); break;
     }
 }
 
@@ -466,7 +470,7 @@ long long stage_tiles(const bub_ctx *c)
 bool stage_fusable(const bub_ctx *c)
 {
     // (a viscous or source pass after the stage changes the state the epilogue would describe)
-    if (!c->d_P2 || slots_for(c->N) != 1 || c->opts.viscous || c->src_on || ct_of(c) == CT_POLY) return false;
+    if (!c->d_P2 || slots_for(c->N, c->nb) != 1 || c->opts.viscous || c->src_on || ct_of(c) == CT_POLY) return false;
     // 3D FP64: the epilogue pays in the balanced-tile kernel of polytropic air (256^3 x 21 split: 42.3 against
     // 44.0 ms a step); in the older kernel its registers cost the stage more than the pass it saves (13.6 ms
     // against 11.9 + 1.5 ms)
@@ -549,7 +553,7 @@ void ctx_buffer_layout(int ndim, long long N, size_t *off_sc, size_t *off_P, siz
     const size_t pbytes = align256(sizeof(double) * (size_t)(ndim + 6) * (size_t)N);
     *off_sc = align256(sizeof(double) * BIN_FIELDS * NB_MAX);
     *off_P = *off_sc + align256(sizeof(Scalars));
-    *off_P2 = slots_for(N) == 1 ? *off_P + pbytes : 0;
+    *off_P2 = slots_for(N, NB_MAX) == 1 ? *off_P + pbytes : 0;
     *total = *off_P + pbytes + (*off_P2 ? pbytes : 0);
 }
 
@@ -708,7 +712,7 @@ int bub_ctx_create(const bub_grid *grid, const bub_liquid *liq, const bub_gas *g
     c->owns = true;
     if (hipMalloc(&c->d_bins, sizeof(double) * BIN_FIELDS * NB_MAX) != hipSuccess ||
         hipMalloc(&c->d_P, pbytes) != hipSuccess || hipMalloc(&c->d_sc, sizeof(Scalars)) != hipSuccess ||
-        (slots_for(c->N) == 1 && hipMalloc(&c->d_P2, pbytes) != hipSuccess)) {
+        (slots_for(c->N, c->nb) == 1 && hipMalloc(&c->d_P2, pbytes) != hipSuccess)) {
         bub_ctx_destroy(c);
         return BUB_ENOMEM;
     }
@@ -1479,7 +1483,7 @@ struct bub_batch {
     size_t budget = 0, used_bytes = 0;            // device bytes of the members; budget 0 = none
     BatchMember *d_tab = nullptr;                 // device member table [max_cases]
     LaunchList *d_lists = nullptr;                // device launch lists [NLISTS]
-    static constexpr int NLISTS = 48;
+    static constexpr int NLISTS = 64;   // kernel classes: 18 + 18 of the passes, 15 stage shapes, the step
     int *h_flags = nullptr, *d_flags = nullptr;   // completion flags in pinned host memory [max_cases]
     // table and list uploads: a ring of pinned staging buffers, each reused only after the event
     // recorded behind its last upload has completed
@@ -1923,10 +1927,6 @@ int bub_rhs_stage_noalloc(const bub_grid *grid, const bub_liquid *liq, const bub
 // ---------------------------------------------------------------------------
 namespace {
 
-constexpr int PRIM_CELLS_1 = 256, PRIM_CELLS_S = 64;   // cells per primitive/bubble block (as launch_prim)
-
-int cells_for(int S) { return S == 1 ? PRIM_CELLS_1 : PRIM_CELLS_S; }
-
 // The member's view for the grouped kernels; the stage decomposition is the one its own launch uses.
 int member_desc(const bub_batch::Member &m, BatchMember *d)
 {
@@ -1975,9 +1975,9 @@ int batch_rebuild(bub_batch *b, hipStream_t s)
         int rc = member_desc(m, &tab[i]);
         if (rc) return rc;
         const bub_ctx *c = m.ctx;
-        const int S = slots_for(c->N);
+        const int S = slots_for(c->N, c->nb);
         pm.push_back({(int)i, c->ndim, S, shape_of(c), c->opts.bubble_mode == BUB_BUBBLES_SPLIT,
-                      (c->N + cells_for(S) - 1) / cells_for(S), (long long)tab[i].nitems});
+                      (c->N + slot_cells(S) - 1) / slot_cells(S), (long long)tab[i].nitems});
     }
     BatchPlan plan;
     if (plan_batch(pm, bub_batch::NLISTS, &plan)) return BUB_EUNSUPPORTED;
@@ -2003,16 +2003,23 @@ int batch_rebuild(bub_batch *b, hipStream_t s)
     return BUB_OK;
 }
 
+template <int D, int MODE, int S>
+void launch_prim_group_s(const bub_batch *b, const bub_batch::Launch &l, int which, hipStream_t s)
+{
+    hipLaunchKernelGGL((k_prim_group<D, MODE, S, slot_cells(S)>), dim3((unsigned)l.blocks), dim3(S * slot_cells(S)), 0, s,
+                       b->d_tab, b->d_lists + l.list, which);
+}
+
 template <int D, int MODE>
 void launch_prim_group(const bub_batch *b, const bub_batch::Launch &l, int which, hipStream_t s)
 {
-    const dim3 grid((unsigned)l.blocks);
-    const LaunchList *L = b->d_lists + l.list;
     switch (l.key) {
-    case 1: hipLaunchKernelGGL((k_prim_group<D, MODE, 1, PRIM_CELLS_1>), grid, dim3(PRIM_CELLS_1), 0, s, b->d_tab, L, which); break;
-    case 2: hipLaunchKernelGGL((k_prim_group<D, MODE, 2, PRIM_CELLS_S>), grid, dim3(2 * PRIM_CELLS_S), 0, s, b->d_tab, L, which); break;
-    case 4: hipLaunchKernelGGL((k_prim_group<D, MODE, 4, PRIM_CELLS_S>), grid, dim3(4 * PRIM_CELLS_S), 0, s, b->d_tab, L, which); break;
-    default: hipLaunchKernelGGL((k_prim_group<D, MODE, 8, PRIM_CELLS_S>), grid, dim3(8 * PRIM_CELLS_S), 0, s, b->d_tab, L, which); break;
+    case 1: launch_prim_group_s<D, MODE, 1>(b, l, which, s); break;
+    case 2: launch_prim_group_s<D, MODE, 2>(b, l, which, s); break;
+    case 4: launch_prim_group_s<D, MODE, 4>(b, l, which, s); break;
+    case 8: launch_prim_group_s<D, MODE, 8>(b, l, which, s); break;
+    case 16: launch_prim_group_s<D, MODE, 16>(b, l, which, s); break;
+    default: launch_prim_group_s<D, MODE, 32>(b, l, which, s); break;
     }
 }
 
@@ -2025,16 +2032,23 @@ void prim_groups(const bub_batch *b, const std::vector<bub_batch::Launch> &v, in
     }
 }
 
+template <int D, int S>
+void launch_bubble_group_s(const bub_batch *b, const bub_batch::Launch &l, hipStream_t s)
+{
+    hipLaunchKernelGGL((k_bubble_group<D, S, slot_cells(S)>), dim3((unsigned)l.blocks), dim3(S * slot_cells(S)), 0, s,
+                       b->d_tab, b->d_lists + l.list);
+}
+
 template <int D>
 void launch_bubble_group(const bub_batch *b, const bub_batch::Launch &l, hipStream_t s)
 {
-    const dim3 grid((unsigned)l.blocks);
-    const LaunchList *L = b->d_lists + l.list;
     switch (l.key) {
-    case 1: hipLaunchKernelGGL((k_bubble_group<D, 1, PRIM_CELLS_1>), grid, dim3(PRIM_CELLS_1), 0, s, b->d_tab, L); break;
-    case 2: hipLaunchKernelGGL((k_bubble_group<D, 2, PRIM_CELLS_S>), grid, dim3(2 * PRIM_CELLS_S), 0, s, b->d_tab, L); break;
-    case 4: hipLaunchKernelGGL((k_bubble_group<D, 4, PRIM_CELLS_S>), grid, dim3(4 * PRIM_CELLS_S), 0, s, b->d_tab, L); break;
-    default: hipLaunchKernelGGL((k_bubble_group<D, 8, PRIM_CELLS_S>), grid, dim3(8 * PRIM_CELLS_S), 0, s, b->d_tab, L); break;
+    case 1: launch_bubble_group_s<D, 1>(b, l, s); break;
+    case 2: launch_bubble_group_s<D, 2>(b, l, s); break;
+    case 4: launch_bubble_group_s<D, 4>(b, l, s); break;
+    case 8: launch_bubble_group_s<D, 8>(b, l, s); break;
+    case 16: launch_bubble_group_s<D, 16>(b, l, s); break;
+    default: launch_bubble_group_s<D, 32>(b, l, s); break;
     }
 }
 

@@ -3,7 +3,7 @@
 //  k_init     primitives -> conserved state, bubbles at equilibrium.
 //  k_prim     per cell: conserved -> primitive scratch P (rho, u, p_l, alpha,
 //             n, B, alpha source), bin moments, optional CFL wave-speed max,
-//             or the 8 diagnostic moments.  On small grids PRIM_SLOTS threads
+//             or the 8 diagnostic moments.  On small grids up to PRIM_SLOTS threads
 //             per cell share its bins (one wave finishes the cells from the
 //             slot sums); large grids take one thread per cell.  Coalesced
 //             structure-of-arrays loads, each bin read once.
@@ -54,7 +54,7 @@ __device__ __forceinline__ double add_plain(double a, double b)
 
 enum PrimMode { PRIM_ONLY = 0, PRIM_CFL = 1, PRIM_MOMENTS = 2 };
 
-constexpr int PRIM_SLOTS = 8;   // threads per cell in the primitive pass
+constexpr int PRIM_SLOTS = 32;   // most threads per cell in the primitive pass
 
 // Bin sums of the primitive pass in the conserved variables x = nR, y = nRdot.  With R = x/n and
 // Rdot = y/n every moment is a power of n times a sum that does not involve n, including the
@@ -252,6 +252,16 @@ __device__ __forceinline__ double prim_finish(const double *__restrict__ q, doub
 // Wavefront max of the CFL wave speed, posted to the workgroup's partial-max slot.
 __device__ inline void cfl_reduce(double wmax, Scalars *sc) { wmax_post(wmax, sc); }
 
+// Slot of this thread in a workgroup of S slots of CELLS cells (a wavefront's where CELLS is its width, so that the
+// bins' tables are read by scalar loads).
+template <int S, int CELLS>
+__device__ __forceinline__ int slot_of()
+{
+    if constexpr (S == 1) return 0;
+    else if constexpr (CELLS == 64) return __builtin_amdgcn_readfirstlane(threadIdx.x / CELLS);
+    else return (int)threadIdx.x / CELLS;
+}
+
 // Primitive pass; grid = ceil(N / CELLS) workgroups of CELLS * S threads.  A workgroup owns CELLS
 // consecutive cells; thread (cell, slot) sums the bins slot, slot + S, ... (each wave reads
 // consecutive cells of one bin).  With S > 1 the slots post their sums to LDS and bump the cell's
@@ -266,7 +276,7 @@ __device__ __forceinline__ void prim_block(const double *__restrict__ q, double 
                                            const double *__restrict__ s_pp)
 {
     const int cl = S == 1 ? (int)threadIdx.x : (int)threadIdx.x % CELLS;
-    const int slot = S == 1 ? 0 : (int)threadIdx.x / CELLS;
+    const int slot = slot_of<S, CELLS>();
     const long long N = g.N;
     const long long c = blk * CELLS + cl;
     const bool live = c < N;
@@ -322,13 +332,21 @@ __global__ void __launch_bounds__(S * CELLS) k_prim(const double *__restrict__ q
     prim_block<D, MODE, S, CELLS, CT>(q, out, g, ph, bins, sc, blockIdx.x, s_pp);
 }
 
-// Threads per cell for a grid of N cells: enough to give about 2^19 threads, at most PRIM_SLOTS.
-__host__ __device__ inline int slots_for(long long N)
+// Threads per cell for a grid of N cells and nb bins: enough to give about 2^19 threads, at most 8; on grids that
+// leave most of the chip idle even so (fewer than 2^17 threads: two wavefronts a SIMD) up to PRIM_SLOTS, as the
+// passes then take as long as one thread's bins do, one after the other (split step of 2000 cells x 31 bins: 59 us
+// with 8 threads a cell, 53 with 32; below 2^18 the batch of 12 x 1200 cells loses 3%).  No more than the bins need.
+__host__ __device__ inline int slots_for(long long N, int nb)
 {
     int s = 1;
-    while (s < PRIM_SLOTS && N * s < (1LL << 19)) s *= 2;
+    while (s < 8 && N * s < (1LL << 19)) s *= 2;
+    if (s == 8)
+        while (s < PRIM_SLOTS && s < nb && N * s < (1LL << 17)) s *= 2;
     return s;
 }
+
+// Cells of a workgroup of the passes with S threads per cell.
+__host__ __device__ constexpr int slot_cells(int S) { return S == 1 ? 256 : S <= 8 ? 64 : 512 / S; }
 
 template <int D>
 __global__ void __launch_bounds__(256) k_init(const double *__restrict__ prim, double *__restrict__ q,

@@ -167,7 +167,7 @@ __device__ __forceinline__ void bubble_block(const BubbleArgs &A, const Grid &g,
                                              Scalars *sc, long long blk)
 {
     const int cl = S == 1 ? (int)threadIdx.x : (int)threadIdx.x % CELLS;
-    const int slot = S == 1 ? 0 : (int)threadIdx.x / CELLS;
+    const int slot = slot_of<S, CELLS>();
     const long long N = g.N;
     const long long c = blk * CELLS + cl;
     const bool live = c < N;

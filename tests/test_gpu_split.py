@@ -192,3 +192,34 @@ def test_steps_in_one_call_are_single_steps(n, contents):
         assert ctx.last_error()[0] == 0
         outs.append(q)
     assert torch.equal(outs[0], outs[1])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,nb", [(8191, 31), (8192, 21), (16383, 9), (60, 17)])
+def test_half_steps_of_many_threads_per_cell(orc, n, nb):
+    """Half-steps with 16 and 32 threads a cell, on both sides of the sizes where the number changes, against the
+    oracle (the bound of the other half-steps), and in a call of several steps against single steps (the same bits)."""
+    import torch
+    import paper_2511_21031_amd as bub
+    case = W.random_smooth(1, (n,), 1e-4, nb, seed=52, bc=1, amp_atm=1.0)
+    pb = orc.problem_from_case(case, split=1)
+    q0 = perturb_bins(orc.init_state(pb, case.prim), 1, nb, seed=8, amp_r=0.02, vel=0.05)
+    tau = 0.5 * orc.cfl_dt(pb, q0)
+    q_ref = q0.copy()
+    ns_ref = orc.bubble_advance(pb, q_ref, tau)
+    ctx = bub.context_from_case(case, bubble_mode=bub.BUBBLES_SPLIT)
+    qg = _gpu(torch, q0)
+    ns = torch.zeros((nb, n), dtype=torch.int32, device="cuda")
+    ctx.bubble_advance(qg, tau, ns)
+    assert ctx.last_error()[0] == 0
+    _compare_advance(qg.cpu().numpy(), q_ref, ns.cpu().numpy(), ns_ref, 1, nb)
+    outs = []
+    for calls in ((3,), (1, 1, 1)):
+        ctx = bub.context_from_case(case, bubble_mode=bub.BUBBLES_SPLIT)
+        q = ctx.init_state(torch.from_numpy(case.prim).cuda())
+        work = ctx.new_work()
+        for k in calls:
+            ctx.rk3_steps(q, work, k)
+        assert ctx.last_error()[0] == 0
+        outs.append(q)
+    assert torch.equal(outs[0], outs[1])

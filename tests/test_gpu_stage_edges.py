@@ -111,3 +111,11 @@ def test_liquid_tiles_inside_the_grid(torch, bub, orc, bc, n):
     scale[1:4] += np.abs(prim[4]).max() / dx
     err = np.abs(got - ref).max(axis=1) / scale
     assert err.max() < 1e-12, err
+
+
+@pytest.mark.parametrize("contents", [False, True])
+@pytest.mark.parametrize("n,nb", [(8191, 31), (8192, 31), (16383, 9), (16384, 17), (60, 17), (40, 7)])
+def test_threads_per_cell_of_the_passes(torch, bub, orc, n, nb, contents):
+    """Primitive passes with 8, 16 and 32 threads a cell, on both sides of the sizes where the number changes, bins
+    that fill the threads and bins that do not: the sources of the right-hand side come from their sums."""
+    _check(torch, bub, orc, (n,), 0, contents, nb, everywhere=True)
