@@ -207,19 +207,40 @@ int launch_prim(bub_ctx *c, const double *q, double *out, int mode, hipStream_t 
     return hipGetLastError() == hipSuccess ? BUB_OK : BUB_EHIP;
 }
 
-// Bin groups: small grids give each tile several workgroups (a range of bins each) so the launch
-// still fills the chip; large grids keep one workgroup per tile (no repeated mixture faces).
+// What a stage of nw workgroups of `waves` wavefronts takes on 256 CUs when each does `bins` bins, in units of one
+// bin of a workgroup alone (1.35 us in 2D): the mixture faces cost about ten bins, whatever the tiles; a CU's second
+// workgroup (of four wavefronts) hides in the first one's waits for the most part, `second`, and k take k times
+// `share`.  Fitted to 60 to 1056 tiles of 2D with 5 to 31 bins, and to 3D boxes of 26^3 to 80^3; FP32 fluxes (light)
+// leave more room.
+double stage_cost(long long nw, int waves, double bins, double second, double share)
+{
+    const long long k = (nw + 255) / 256 * ((waves + 3) / 4);
+    return (10.0 + bins) * (k == 1 ? 1.0 : k == 2 ? second : share * (double)k);
+}
+
+double group_cost(long long nw, int waves, int bins, bool light)
+{
+    return light ? stage_cost(nw, waves, bins, 1.2, 0.43) : stage_cost(nw, waves, bins, 1.3, 0.6);
+}
+
+// Bin groups: small grids give each tile several workgroups (a range of bins each) where the cheaper bins outweigh
+// the repeated mixture faces (group_cost).  About 1024 workgroups, the rule before, was too many: a viscous step of
+// 600 x 150 x 5 with 3, 2, 1 groups 185, 164, 158 us, of 300 x 100 x 31 with 8, 4, 3 groups 190, 179, 170, of
+// 150 x 80 x 31 with 16, 4, 3 groups 152, 135, 145.
 // Returns the bins per group; *groups receives the workgroups per tile.
-int bin_grouping(const bub_ctx *c, long long ntiles, int *groups)
+int bin_grouping(const bub_ctx *c, long long ntiles, int waves, int *groups)
 {
     int ng = c->bin_groups;
     if (ng <= 0) {
-        constexpr int target = 1024;   // work items that keep 256 CUs busy
-        ng = ntiles >= target ? 1 : (int)((target + ntiles - 1) / ntiles);
-        const int cap = (c->nb + 1) / 2;  // at least two bins per group
-        if (ng > cap) ng = cap;
+        ng = 1;
+        const bool light = c->opts.precision == BUB_PREC_MIXED;
+        double best = group_cost(ntiles, waves, c->nb, light);
+        const int cap = (c->nb + 1) / 2;   // at least two bins per group
+        for (int g = 2; g <= cap && ntiles * (g - 1) < 1024; ++g) {
+            const double t = group_cost(ntiles * g, waves, (c->nb + g - 1) / g, light);
+            if (t < best) best = t, ng = g;
+        }
     }
-    if (ng < 1) ng = 1;
     if (ng > c->nb) ng = c->nb;
     const int bpg = (c->nb + ng - 1) / ng;
     *groups = (c->nb + bpg - 1) / bpg;
@@ -235,8 +256,8 @@ int launch_stage_t(bub_ctx *c, StageArgs A, hipStream_t s)
     A.ntile[1] = (c->g.n[1] + G::TY - 1) / G::TY;
     A.ntile[2] = (c->g.n[2] + G::TZ - 1) / G::TZ;
     A.ntiles = A.ntile[0] * A.ntile[1] * A.ntile[2];
-    A.bpg = bin_grouping(c, A.ntiles, &A.ngroups);
-    if (A.Pout && A.ngroups != 1) return BUB_EINVAL;   // the fused epilogue needs every bin of a cell
+    A.bpg = bin_grouping(c, A.ntiles, TC::BLOCK / 64, &A.ngroups);
+    if (A.Pout) A.bpg = c->nb, A.ngroups = 1;   // the fused epilogue needs every bin of a cell
     A.nitems = A.ntiles * A.ngroups;
     A.nblk_per_xcd = (A.nitems + 7) / 8;
     if (tile_ok(c, V)) {
@@ -456,28 +477,53 @@ int stage(bub_ctx *c, const StageArgs &A, hipStream_t s, double tc)
     return BUB_OK;
 }
 
-// Tiles of the context's current stage shape.
-long long stage_tiles(const bub_ctx *c)
+// Tiles of the context's current stage shape, and the wavefronts of a workgroup.
+long long stage_tiles(const bub_ctx *c, int *waves)
 {
     int tx, ty, tz, blk;
     bub_tile_info(c, kernel_shape(c), &tx, &ty, &tz, &blk);
+    *waves = blk / 64;
     return (long long)((c->g.n[0] + tx - 1) / tx) * ((c->g.n[1] + ty - 1) / ty) * ((c->g.n[2] + tz - 1) / tz);
 }
 
+// Cells from which a context that allocates its own memory keeps the second primitive scratch.
+constexpr long long FUSE_CELLS = 1 << 14;
+
+// Whether a grid of fewer than 2^19 cells is better off with one workgroup per tile that carries the primitive pass
+// than with its bins in groups and a pass of its own (six bins and 10,000 cells a bin).  Microseconds a step, apart
+// over fused: FP64 200^2 x 11 131 / 95, x 31 151 / 174, 320^2 x 31 266 / 228, 500^2 x 31 542 / 520; mixed 200^2 x 11
+// 109 / 90, x 31 129 / 166, 320^2 x 31 232 / 209, 450^2 x 31 397 / 364, 500^2 x 31 473 / 490; 3D x 11 FP64 32^3
+// 171 / 122, mixed 107 / 146, 40^3 230 / 150, 64^3 x 31 753 / 849.
+bool fuse_pays(const bub_ctx *c)
+{
+    if (c->bin_groups > 0 || c->ndim == 1 || !tile_ok(c, kernel_shape(c))) return false;
+    int waves, groups;
+    const long long nt = stage_tiles(c, &waves);
+    const int bpg = bin_grouping(c, nt, waves, &groups);
+    const bool light = c->opts.precision == BUB_PREC_MIXED;
+    const double fused = stage_cost(nt, waves, (light ? 1.1 : 1.15) * c->nb, 1.3, light ? 0.53 : 0.6);
+    return fused < group_cost(nt * groups, waves, bpg, light) + 6.0 + (double)c->N / 10000.0;
+}
+
 // The stage kernels can carry the primitive pass of the state they write (fused epilogue) when one
-// workgroup owns all bins of a tile and the grid is large enough that the primitive pass would take
-// one thread per cell (then both forms sum the bins in the same order, so results are bitwise equal).
+// workgroup owns all bins of a tile.  The tile kernels sum the bins in the order of the grid's primitive
+// pass, the others only in that of one thread per cell, so results are bitwise those of separate passes.
 bool stage_fusable(const bub_ctx *c)
 {
     // (a viscous or source pass after the stage changes the state the epilogue would describe)
-    if (!c->d_P2 || slots_for(c->N, c->nb) != 1 || c->opts.viscous || c->src_on || ct_of(c) == CT_POLY) return false;
+    if (!c->d_P2 || c->opts.viscous || c->src_on || ct_of(c) == CT_POLY) return false;
     // 3D FP64: the epilogue pays in the balanced-tile kernel of polytropic air (256^3 x 21 split: 42.3 against
     // 44.0 ms a step); in the older kernel its registers cost the stage more than the pass it saves (13.6 ms
     // against 11.9 + 1.5 ms)
     if (c->ndim == 3 && c->opts.precision == BUB_PREC_FP64 && !(pw_fast(c) && tile_ok(c, kernel_shape(c)))) return false;
-    int groups = 0, nt;
-    if (uses_line(c)) line_grouping(c, &nt, &groups);
-    else bin_grouping(c, stage_tiles(c), &groups);
+    if (slots_for(c->N, c->nb) != 1) return fuse_pays(c);
+    int groups = 0, nt, waves;
+    if (uses_line(c)) {
+        line_grouping(c, &nt, &groups);
+    } else {
+        const long long tiles = stage_tiles(c, &waves);
+        bin_grouping(c, tiles, waves, &groups);
+    }
     return groups == 1;
 }
 
@@ -546,8 +592,8 @@ __global__ void k_err_copy(const Scalars *sc, int64_t *dst)
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Device-buffer layout of a context: bin table | scalars | primitive scratch | second primitive
-// scratch (only for grids of 2^19 cells or more, whose stages carry the primitive pass; off_P2 = 0
-// otherwise).
+// scratch (on a caller's buffer only for grids of 2^19 cells or more, whose stages carry the primitive
+// pass; off_P2 = 0 otherwise).
 void ctx_buffer_layout(int ndim, long long N, size_t *off_sc, size_t *off_P, size_t *off_P2, size_t *total)
 {
     const size_t pbytes = align256(sizeof(double) * (size_t)(ndim + 6) * (size_t)N);
@@ -712,7 +758,7 @@ int bub_ctx_create(const bub_grid *grid, const bub_liquid *liq, const bub_gas *g
     c->owns = true;
     if (hipMalloc(&c->d_bins, sizeof(double) * BIN_FIELDS * NB_MAX) != hipSuccess ||
         hipMalloc(&c->d_P, pbytes) != hipSuccess || hipMalloc(&c->d_sc, sizeof(Scalars)) != hipSuccess ||
-        (slots_for(c->N, c->nb) == 1 && hipMalloc(&c->d_P2, pbytes) != hipSuccess)) {
+        ((slots_for(c->N, c->nb) == 1 || (c->ndim > 1 && c->N >= FUSE_CELLS)) && hipMalloc(&c->d_P2, pbytes) != hipSuccess)) {
         bub_ctx_destroy(c);
         return BUB_ENOMEM;
     }
@@ -902,6 +948,7 @@ int rk3_steps_impl(bub_ctx *c, double *q, double *work, int nsteps, double dt, d
         A.rhs_mode = 0;
         A.sources = split ? 0 : 1;
         A.sc = c->d_sc;
+        A.slots = slots_for(c->N, c->nb);
         // stage 1: u1 = u^n + dt L(u^n)
         A.qk = q; A.qn = nullptr; A.qo = w1; A.a = 0.0; A.b = 1.0;
         A.P = Pa;
@@ -1952,7 +1999,7 @@ int member_desc(const bub_batch::Member &m, BatchMember *d)
     d->ntile[1] = (c->g.n[1] + ty - 1) / ty;
     d->ntile[2] = (c->g.n[2] + tz - 1) / tz;
     d->ntiles = d->ntile[0] * d->ntile[1] * d->ntile[2];
-    d->bpg = bin_grouping(c, d->ntiles, &d->ngroups);
+    d->bpg = bin_grouping(c, d->ntiles, blk / 64, &d->ngroups);
     d->nitems = d->ntiles * d->ngroups;
     return BUB_OK;
 }

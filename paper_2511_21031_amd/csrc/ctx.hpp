@@ -26,7 +26,7 @@ struct bub_ctx {
     double h_pb0[bub::NB_MAX]{}, h_mv0[bub::NB_MAX]{}, h_mg[bub::NB_MAX]{};   // transfer contents
     double *d_bins = nullptr;    // [BIN_FIELDS][nb]: r0, w, pg0, pb0, mv0, mg
     double *d_P = nullptr;       // [nprim][N] primitive scratch
-    double *d_P2 = nullptr;      // second primitive scratch of the fused stages (grids of 2^19 cells or more)
+    double *d_P2 = nullptr;      // second primitive scratch of the fused stages, or null
     bub::Scalars *d_sc = nullptr;
     bub::Phys ph{};
     bub::Grid g{};

@@ -25,6 +25,7 @@ struct StageArgs {
     // the state it produces into Pout (the layout of P; must not be P) and, with cfl set, posts that
     // state's wave-speed maximum.  Null Pout: the next stage needs a primitive pass of its own.
     double *Pout;
+    int slots;          // threads per cell of the grid's primitive pass, whose order of bins the epilogue keeps
     int cfl;
     Scalars *sc;        // error word and wave-speed maxima of the context
 };

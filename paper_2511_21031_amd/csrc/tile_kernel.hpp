@@ -64,6 +64,8 @@ __global__ void __launch_bounds__(BLOCK) k_tile(StageArgs A, Grid g, Phys ph, Bi
     PT *s_q = reinterpret_cast<PT *>(s_mem);             // [NP][QCELLS]
     PT *s_f = reinterpret_cast<PT *>(s_mem + QBYTES);    // [NP][D][BLOCK]
     TF *s_c = reinterpret_cast<TF *>(s_mem);             // [NCF][D][BLOCK]
+    // the epilogue's bin sums of the slots that are done (an owned cell's are its thread's)
+    __shared__ double s_tot[FUSE ? 5 : 1][FUSE ? T : 1];
 
     // XCD-aware order: consecutive items (and the bin groups of a tile) land on the same XCD
     const int item = (int)(blockIdx.x & 7) * A.nblk_per_xcd + (int)(blockIdx.x >> 3);
@@ -219,10 +221,25 @@ __global__ void __launch_bounds__(BLOCK) k_tile(StageArgs A, Grid g, Phys ph, Bi
     __syncthreads();   // the mixture fluxes' space is the bins' from here
 
     // ---- bins ----
+    // The fused epilogue adds the bins up as the primitive pass of this grid does, whose A.slots threads a cell take
+    // the bins slot, slot + slots, ..., so it walks them in that order (one slot: in plain order) and puts a slot's
+    // sums by when it is done.
     [[maybe_unused]] BinSums acc;
     acc.bad = nb;
+    [[maybe_unused]] int bad = nb, slot = 0;
+    const int slots = FUSE ? A.slots : 1;
+    int next = b0;
 #pragma unroll 1
-    for (int ib = b0; ib < b1; ++ib) {
+    for (int it = b0; it < b1; ++it) {
+        const int ib = next;
+        next = ib + slots;
+        bool turn = false;   // the slot's last bin
+        if constexpr (FUSE) {
+            if (next >= b1) {
+                turn = true;
+                next = ++slot;
+            }
+        }
         const double r0 = bins.r0[ib], pg0 = bins.pg0[ib];
 #pragma unroll
         for (int r = 0; r < CPT; ++r)
@@ -247,7 +264,7 @@ __global__ void __launch_bounds__(BLOCK) k_tile(StageArgs A, Grid g, Phys ph, Bi
 #pragma unroll
             for (int f = 0; f < NF; ++f) un[f] = A.qn[(long long)(D + 3 + f * nb + ib) * N + st_g[0]];
         }
-        if (ib + 1 < b1) load(ib + 1);
+        if (it + 1 < b1) load(next);
 #pragma unroll
         for (int d = 0; d < D; ++d) {
             const int at = fa[d] & 0xffff, sd = fa[d] >> 16;
@@ -317,6 +334,18 @@ __global__ void __launch_bounds__(BLOCK) k_tile(StageArgs A, Grid g, Phys ph, Bi
             }
 #pragma unroll
             for (int f = 0; f < NF; ++f) A.qo[(long long)(D + 3 + f * nb + ib) * N + c] = out[f];
+            if constexpr (FUSE) {
+                if (turn && it + 1 < b1) {
+                    double *v[5] = {&acc.s3, &acc.s2, &acc.s21, &acc.s32, &acc.sp};
+#pragma unroll
+                    for (int k = 0; k < 5; ++k) {
+                        s_tot[k][oc] = slot > 1 ? s_tot[k][oc] + *v[k] : *v[k];
+                        *v[k] = 0.0;
+                    }
+                    bad = acc.bad < bad ? acc.bad : bad;
+                    acc.bad = nb;
+                }
+            }
         }
         // the next bin is staged only after every thread has passed the barrier above, and its fluxes are
         // posted only after the barrier that follows its staging
@@ -324,6 +353,14 @@ __global__ void __launch_bounds__(BLOCK) k_tile(StageArgs A, Grid g, Phys ph, Bi
     if constexpr (FUSE) {
         // the primitive pass of the new state for the owned cell (same arithmetic as k_prim)
         if (act) {
+            if (slot > 1) {
+                acc.s3 = s_tot[0][oc] + acc.s3;
+                acc.s2 = s_tot[1][oc] + acc.s2;
+                acc.s21 = s_tot[2][oc] + acc.s21;
+                acc.s32 = s_tot[3][oc] + acc.s32;
+                acc.sp = s_tot[4][oc] + acc.sp;
+                acc.bad = acc.bad < bad ? acc.bad : bad;
+            }
             const CellBins m = cell_bins<CT>(new_rho, new_a, acc, ph, bins);
             A.Pout[(long long)PL<D>::N * N + c] = m.n;
             A.Pout[(long long)PL<D>::B * N + c] = m.B;

@@ -119,3 +119,25 @@ def test_threads_per_cell_of_the_passes(torch, bub, orc, n, nb, contents):
     """Primitive passes with 8, 16 and 32 threads a cell, on both sides of the sizes where the number changes, bins
     that fill the threads and bins that do not: the sources of the right-hand side come from their sums."""
     _check(torch, bub, orc, (n,), 0, contents, nb, everywhere=True)
+
+
+CARRY = [((211, 203), 11, False, False), ((211, 203), 11, True, False), ((127, 190), 5, False, True), ((331, 320), 31, False, False),
+         ((41, 40, 39), 11, False, False), ((41, 40, 39), 11, True, False), ((64, 33, 30), 5, False, True)]
+
+
+@pytest.mark.parametrize("split", [False, True])
+@pytest.mark.parametrize("n,nb,mixed,contents", CARRY)
+def test_stages_of_small_grids_that_carry_their_primitives(torch, bub, n, nb, mixed, contents, split):
+    """Grids whose primitive pass takes two to eight threads a cell: a stage that carries it adds the bins up in that
+    pass's order.  Three steps in one call, bitwise those with the bins in two groups and a pass of their own."""
+    case = _case(n, 1, contents, nb)
+    outs = []
+    for groups in (0, 2):
+        ctx = bub.context_from_case(case, precision=bub.PREC_MIXED if mixed else bub.PREC_FP64,
+                                    bubble_mode=bub.BUBBLES_SPLIT if split else bub.BUBBLES_UNSPLIT)
+        ctx.set_bin_groups(groups)
+        q = ctx.init_state(torch.from_numpy(case.prim).cuda())
+        ctx.rk3_steps(q, ctx.new_work(), 3)
+        assert ctx.last_error()[0] == 0
+        outs.append(q)
+    assert torch.equal(outs[0], outs[1])
