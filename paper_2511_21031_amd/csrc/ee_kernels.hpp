@@ -335,11 +335,12 @@ __global__ void __launch_bounds__(S * CELLS) k_prim(const double *__restrict__ q
 // Threads per cell for a grid of N cells and nb bins: enough to give about 2^19 threads, at most 8; on grids that
 // leave most of the chip idle even so (fewer than 2^17 threads: two wavefronts a SIMD) up to PRIM_SLOTS, as the
 // passes then take as long as one thread's bins do, one after the other (split step of 2000 cells x 31 bins: 59 us
-// with 8 threads a cell, 53 with 32; below 2^18 the batch of 12 x 1200 cells loses 3%).  No more than the bins need.
+// with 8 threads a cell, 53 with 32; below 2^18 the batch of 12 x 1200 cells loses 3%).  Threads without bins only
+// cost: ten viscous steps of 600 x 150 x 5 took 1335 us with 8 threads a cell, 1229 with 4.
 __host__ __device__ inline int slots_for(long long N, int nb)
 {
     int s = 1;
-    while (s < 8 && N * s < (1LL << 19)) s *= 2;
+    while (s < 8 && 2 * s <= nb + 1 && N * s < (1LL << 19)) s *= 2;
     if (s == 8)
         while (s < PRIM_SLOTS && s < nb && N * s < (1LL << 17)) s *= 2;
     return s;
