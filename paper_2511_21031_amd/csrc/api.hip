@@ -756,12 +756,16 @@ int bub_ctx_create(const bub_grid *grid, const bub_liquid *liq, const bub_gas *g
     if (rc) return rc;
     size_t pbytes = sizeof(double) * (size_t)c->nprim * (size_t)c->N;
     c->owns = true;
+    // the second primitive scratch, where stages can carry the pass, is the rest of the first one's allocation (an
+    // allocation of its own takes some 75 us)
+    const size_t p2 = align256(pbytes);
+    const bool two = slots_for(c->N, c->nb) == 1 || (c->ndim > 1 && c->N >= FUSE_CELLS && !c->opts.viscous && ct_of(c) != CT_POLY);
     if (hipMalloc(&c->d_bins, sizeof(double) * BIN_FIELDS * NB_MAX) != hipSuccess ||
-        hipMalloc(&c->d_P, pbytes) != hipSuccess || hipMalloc(&c->d_sc, sizeof(Scalars)) != hipSuccess ||
-        ((slots_for(c->N, c->nb) == 1 || (c->ndim > 1 && c->N >= FUSE_CELLS)) && hipMalloc(&c->d_P2, pbytes) != hipSuccess)) {
+        hipMalloc(&c->d_P, two ? 2 * p2 : pbytes) != hipSuccess || hipMalloc(&c->d_sc, sizeof(Scalars)) != hipSuccess) {
         bub_ctx_destroy(c);
         return BUB_ENOMEM;
     }
+    if (two) c->d_P2 = c->d_P + p2 / sizeof(double);
     double tab[BIN_FIELDS * NB_MAX];
     bin_table(c, tab);
     Scalars zero{};
@@ -826,7 +830,6 @@ int bub_ctx_destroy(bub_ctx *c)
         (void)hipDeviceSynchronize();
         if (c->d_bins) (void)hipFree(c->d_bins);
         if (c->d_P) (void)hipFree(c->d_P);
-        if (c->d_P2) (void)hipFree(c->d_P2);
         if (c->d_sc) (void)hipFree(c->d_sc);
     }
     for (ProfRec &r : c->prof) {
