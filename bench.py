@@ -46,7 +46,7 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_stage_2d1024_nb31_traffic.md")
 
 
 # the sources that define the stage kernel's code (tile shapes are part of the kernel's name)
-STAGE_SOURCES = ("device_common.hpp", "ee_kernels.hpp", "stage_kernel.hpp")
+STAGE_SOURCES = ("device_common.hpp", "ee_kernels.hpp", "stage_args.hpp", "stage_kernel.hpp", "tile_kernel.hpp")
 
 
 def kernel_hash() -> str:
@@ -456,8 +456,9 @@ def stage_run(bub, torch, case, precision, args) -> dict:
            "k_prim_avg_ms": prim_ms / max(prim_n, 1), "k_prim_launches": prim_n,
            "other_avg_ms": other_ms / max(other_n, 1), "other_launches": other_n,
            "tile": [tx, ty, tz, blk], "autotune_ms": [round(m, 4) for m in tile_ms], "nvar": ctx.nvar,
-           "kname": (f"void bub::k_stage<2, {tx}, {ty}, {tz}, {blk}, {tf}, true, 1>" if case.contents is None
-                     else f"void bub::k_stage<2, {tx}, {ty}, {tz}, {blk}, {tf}, true, 2>")}
+           # (with and without the u^n term, the last parameter; transfer contents have one shape)
+           "kname": (f"void bub::k_tile<2, {tx}, {ty}, {tz}, {blk}, {tf}, 3, 1, true>" if case.contents is None
+                     else f"void bub::k_tile<2, 16, 15, 1, 256, {tf}, 2, 1, true>")}
     print(f"[stage] {precision}: {res['ms_per_step']:.3f} ms per step, stage kernel {res['k_stage_avg_ms']:.3f} ms, "
           f"primitive pass {res['k_prim_avg_ms']:.3f} ms x {prim_n}", file=sys.stderr, flush=True)
     del q, work, ctx
