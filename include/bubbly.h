@@ -442,7 +442,8 @@ const char *bub_strerror(int code);
 
 /* Tile shapes of the fused stage kernel.  Each dimensionality has a fixed list
  * of compiled shapes (tile extent tx*ty*tz cells, `block` threads); a context
- * starts on shape 0.  Results do not depend on the shape (each face flux is
+ * starts on the one its dimensionality, precision and contents usually do best
+ * with (shape 0 for the general polytropic power).  Results do not depend on the shape (each face flux is
  * computed by the same arithmetic whichever tile owns it); only speed does.
  * bub_tile_info: shape idx of this context's dimensionality (host outputs).
  * bub_tile_set / bub_tile_get: select / query the shape used by later calls. */
@@ -454,8 +455,9 @@ int bub_tile_get(const bub_ctx *ctx, int *idx);
 /* Bin groups of the fused stage kernel: `groups` workgroups share each tile,
  * each taking a contiguous range of bins (the mixture faces are computed by
  * every group and written by the first).  0 (the default) chooses per launch:
- * one group when the grid has at least 1024 tiles, else enough groups to give
- * about 1024 workgroups, with at least two bins per group.  Results do not
+ * one group on large grids, on small ones the number that weighs the repeated
+ * mixture faces against the bins a workgroup does one after the other, with at
+ * least two bins per group.  Results do not
  * depend on the grouping; only the latency of small problems does.  BUB_EINVAL
  * for groups < 0; values above nb act as nb. */
 int bub_bin_groups(bub_ctx *ctx, int groups);
