@@ -520,9 +520,6 @@ __device__ __forceinline__ void stage_tile(const StageArgs &A, const Grid &g, co
     __syncthreads();  // a following tile on this workgroup may reuse the LDS at once
 }
 
-// The unfused 1D and 2D kernels of the mixed form with the fifth-root power fit 96 VGPRs without
-// spilling and run five waves per SIMD (2D: 4 % faster stage than at four); the FP64 ones, the fused
-// ones and those of the other contents would spill.
 // The LDS arrays of one stage workgroup, declared in the kernel that uses them.
 #define BUB_STAGE_SHARED(D, TX_, TY_, TZ_, BLOCK, TF, NF)                               \
     __shared__ TF s_coef[Geo<D, TX_, TY_, TZ_>::F];                                       \
@@ -545,8 +542,22 @@ __device__ __forceinline__ void stage_item(const StageArgs &A, const Grid &g, co
                                                       s_out, s_pp);
 }
 
+// Wavefronts a SIMD that the register allocation of a stage kernel keeps room for.  The unfused 1D and 2D kernels of
+// the mixed form with the fifth-root power fit 96 VGPRs without spilling and run five (2D: 4 % faster stage than at
+// four); the FP64 ones, the fused ones and those of the other contents would spill.  The 3D kernels of the mixed form
+// sit at the edge of three wavefronts (168 VGPRs), those of 512 threads of four (128), where a CU's second workgroup
+// hangs on it; none spills.  Microseconds a step, left to itself and held: general power 112^3 x 11 3068 and 2466,
+// 8 x 8 x 7 tiles of kappa = 5/3 84^3 x 5 719 and 561.
+template <int D, int BLOCK, typename TF, bool FUSE, int CT>
+__host__ __device__ constexpr int stage_waves()
+{
+    if (sizeof(TF) != 4) return 1;
+    if (D == 3) return BLOCK == 512 ? 4 : 3;
+    return !FUSE && CT == CT_FIFTHS ? 5 : 1;
+}
+
 template <int D, int TX_, int TY_, int TZ_, int BLOCK, typename TF, bool FUSE, int CT>
-__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((D <= 2 && sizeof(TF) == 4 && !FUSE && CT == CT_FIFTHS) ? 5 : 1))) k_stage(StageArgs A, Grid g, Phys ph, Bins bins)
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(stage_waves<D, BLOCK, TF, FUSE, CT>()))) k_stage(StageArgs A, Grid g, Phys ph, Bins bins)
 {
     BUB_STAGE_SHARED(D, TX_, TY_, TZ_, BLOCK, TF, 2)
     // XCD-aware order: consecutive items land on the same XCD (blocks are dealt round-robin), and
