@@ -1960,7 +1960,7 @@ int bub_rhs_stage_noalloc(const bub_grid *grid, const bub_liquid *liq, const bub
     BinTable t{};
     bin_table(&c, t.v);
     // the previous call's contents are overwritten: bin table, cleared error word and maxima
-    hipLaunchKernelGGL(k_ctx_init, dim3(1), dim3(64), 0, s, c.d_bins, t, 3 * c.nb, c.d_sc);
+    hipLaunchKernelGGL(k_ctx_init, dim3(1), dim3(64), 0, s, c.d_bins, t, BIN_FIELDS * c.nb, c.d_sc);
     HIP_OK(hipGetLastError());
     if ((rc = rhs_stage_impl(&c, q, rhs, s))) return rc;
     if (err) {
