@@ -23,6 +23,7 @@
 #include "source_kernel.hpp"
 #include "line.hpp"
 #include "tile.hpp"
+#include "stage_rules.hpp"
 
 #include <vector>
 #include "ctx.hpp"
@@ -207,44 +208,10 @@ int launch_prim(bub_ctx *c, const double *q, double *out, int mode, hipStream_t 
     return hipGetLastError() == hipSuccess ? BUB_OK : BUB_EHIP;
 }
 
-// What a stage of nw workgroups of `waves` wavefronts takes on 256 CUs when each does `bins` bins, in units of one
-// bin of a workgroup alone (1.35 us in 2D): the mixture faces cost about ten bins, whatever the tiles; a CU's second
-// workgroup (of four wavefronts) hides in the first one's waits for the most part, `second`, and k take k times
-// `share`.  Fitted to 60 to 1056 tiles of 2D with 5 to 31 bins, and to 3D boxes of 26^3 to 80^3; FP32 fluxes (light)
-// leave more room.
-double stage_cost(long long nw, int waves, double bins, double second, double share)
-{
-    const long long k = (nw + 255) / 256 * ((waves + 3) / 4);
-    return (10.0 + bins) * (k == 1 ? 1.0 : k == 2 ? second : share * (double)k);
-}
-
-double group_cost(long long nw, int waves, int bins, bool light)
-{
-    return light ? stage_cost(nw, waves, bins, 1.2, 0.43) : stage_cost(nw, waves, bins, 1.3, 0.6);
-}
-
-// Bin groups: small grids give each tile several workgroups (a range of bins each) where the cheaper bins outweigh
-// the repeated mixture faces (group_cost).  About 1024 workgroups, the rule before, was too many: a viscous step of
-// 600 x 150 x 5 with 3, 2, 1 groups 185, 164, 158 us, of 300 x 100 x 31 with 8, 4, 3 groups 190, 179, 170, of
-// 150 x 80 x 31 with 16, 4, 3 groups 152, 135, 145.
-// Returns the bins per group; *groups receives the workgroups per tile.
+// Workgroups per tile (stage_rules.hpp); returns the bins per group.
 int bin_grouping(const bub_ctx *c, long long ntiles, int waves, int *groups)
 {
-    int ng = c->bin_groups;
-    if (ng <= 0) {
-        ng = 1;
-        const bool light = c->opts.precision == BUB_PREC_MIXED;
-        double best = group_cost(ntiles, waves, c->nb, light);
-        const int cap = (c->nb + 1) / 2;   // at least two bins per group
-        for (int g = 2; g <= cap && ntiles * (g - 1) < 1024; ++g) {
-            const double t = group_cost(ntiles * g, waves, (c->nb + g - 1) / g, light);
-            if (t < best) best = t, ng = g;
-        }
-    }
-    if (ng > c->nb) ng = c->nb;
-    const int bpg = (c->nb + ng - 1) / ng;
-    *groups = (c->nb + bpg - 1) / bpg;
-    return bpg;
+    return bins_per_group(ntiles, waves, c->nb, c->opts.precision == BUB_PREC_MIXED, c->bin_groups, groups);
 }
 
 template <int D, int V, typename TF>
@@ -489,22 +456,6 @@ long long stage_tiles(const bub_ctx *c, int *waves)
 // Cells from which a context that allocates its own memory keeps the second primitive scratch.
 constexpr long long FUSE_CELLS = 1 << 14;
 
-// Whether a grid of fewer than 2^19 cells is better off with one workgroup per tile that carries the primitive pass
-// than with its bins in groups and a pass of its own (six bins and 10,000 cells a bin).  Microseconds a step, apart
-// over fused: FP64 200^2 x 11 131 / 95, x 31 151 / 174, 320^2 x 31 266 / 228, 500^2 x 31 542 / 520; mixed 200^2 x 11
-// 109 / 90, x 31 129 / 166, 320^2 x 31 232 / 209, 450^2 x 31 397 / 364, 500^2 x 31 473 / 490; 3D x 11 FP64 32^3
-// 171 / 122, mixed 107 / 146, 40^3 230 / 150, 64^3 x 31 753 / 849.
-bool fuse_pays(const bub_ctx *c)
-{
-    if (c->bin_groups > 0 || c->ndim == 1 || !tile_ok(c, kernel_shape(c))) return false;
-    int waves, groups;
-    const long long nt = stage_tiles(c, &waves);
-    const int bpg = bin_grouping(c, nt, waves, &groups);
-    const bool light = c->opts.precision == BUB_PREC_MIXED;
-    const double fused = stage_cost(nt, waves, (light ? 1.1 : 1.15) * c->nb, 1.3, light ? 0.53 : 0.6);
-    return fused < group_cost(nt * groups, waves, bpg, light) + 6.0 + (double)c->N / 10000.0;
-}
-
 // The stage kernels can carry the primitive pass of the state they write (fused epilogue) when one
 // workgroup owns all bins of a tile.  The tile kernels sum the bins in the order of the grid's primitive
 // pass, the others only in that of one thread per cell, so results are bitwise those of separate passes.
@@ -515,15 +466,19 @@ bool stage_fusable(const bub_ctx *c)
     // 3D FP64: the epilogue pays in the balanced-tile kernel of polytropic air (256^3 x 21 split: 42.3 against
     // 44.0 ms a step); in the older kernel its registers cost the stage more than the pass it saves (13.6 ms
     // against 11.9 + 1.5 ms)
-    if (c->ndim == 3 && c->opts.precision == BUB_PREC_FP64 && !(pw_fast(c) && tile_ok(c, kernel_shape(c)))) return false;
-    if (slots_for(c->N, c->nb) != 1) return fuse_pays(c);
+    const bool tiled = c->ndim > 1 && tile_ok(c, kernel_shape(c)), light = c->opts.precision == BUB_PREC_MIXED;
+    if (c->ndim == 3 && !light && !(pw_fast(c) && tiled)) return false;
+    const bool sources = c->opts.bubble_mode == BUB_BUBBLES_UNSPLIT;
+    if (tiled && fused_starves(c->ndim, light, sources)) return false;
     int groups = 0, nt, waves;
     if (uses_line(c)) {
         line_grouping(c, &nt, &groups);
-    } else {
-        const long long tiles = stage_tiles(c, &waves);
-        bin_grouping(c, tiles, waves, &groups);
+        return slots_for(c->N, c->nb) == 1 && groups == 1;
     }
+    const long long tiles = stage_tiles(c, &waves);
+    if (slots_for(c->N, c->nb) != 1)
+        return tiled && c->bin_groups <= 0 && fused_pays(c->ndim, c->N, tiles, waves, c->nb, light, sources);
+    bin_grouping(c, tiles, waves, &groups);
     return groups == 1;
 }
 
