@@ -211,7 +211,7 @@ int launch_prim(bub_ctx *c, const double *q, double *out, int mode, hipStream_t 
 // Workgroups per tile (stage_rules.hpp); returns the bins per group.
 int bin_grouping(const bub_ctx *c, long long ntiles, int waves, int *groups)
 {
-    return bins_per_group(ntiles, waves, c->nb, c->opts.precision == BUB_PREC_MIXED, c->bin_groups, groups);
+    return bins_per_group(c->ndim, ntiles, waves, c->nb, c->opts.precision == BUB_PREC_MIXED, c->bin_groups, groups);
 }
 
 template <int D, int V, typename TF>

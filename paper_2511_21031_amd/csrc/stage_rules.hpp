@@ -24,12 +24,20 @@ inline double group_cost(long long nw, int waves, int bins, bool light)
 // Bin groups: small grids give each tile several workgroups (a range of bins each) where the cheaper bins outweigh
 // the repeated mixture faces (group_cost).  About 1024 workgroups, the rule before, was too many: a viscous step of
 // 600 x 150 x 5 with 3, 2, 1 groups 185, 164, 158 us, of 300 x 100 x 31 with 8, 4, 3 groups 190, 179, 170, of
-// 150 x 80 x 31 with 16, 4, 3 groups 152, 135, 145.  forced: the caller's number (0: by this rule).
+// 150 x 80 x 31 with 16, 4, 3 groups 152, 135, 145.  In 1D a mixture face has one direction and a tile few halo cells,
+// so a repeat costs less, and the nearest number to 1024 workgroups of four wavefronts is best (kappa = 5/3 FP64:
+// 60000 x 31 with 2, 4, 5 groups 149, 138, 137 us, 100000 x 31 with 1, 3 237, 188, 250000 x 11 with 1, 2 193, 211;
+// 1 % behind the best number on average, 11 % at worst, where group_cost is 8 and 53 %).
+// forced: the caller's number (0: by this rule).
 // Returns the bins per group; *groups receives the workgroups per tile.
-inline int bins_per_group(long long ntiles, int waves, int nb, bool light, int forced, int *groups)
+inline int bins_per_group(int ndim, long long ntiles, int waves, int nb, bool light, int forced, int *groups)
 {
     int ng = forced;
-    if (ng <= 0) {
+    if (ng <= 0 && ndim == 1) {
+        const int cap = (nb + 1) / 2;
+        const long long load = ntiles * waves, want = (4096 + load / 2) / load;
+        ng = want < 1 ? 1 : want > cap ? cap : (int)want;
+    } else if (ng <= 0) {
         ng = 1;
         double best = group_cost(ntiles, waves, nb, light);
         const int cap = (nb + 1) / 2;   // at least two bins per group
@@ -61,7 +69,7 @@ inline bool fused_pays(int ndim, long long cells, long long ntiles, int waves, i
 {
     if (ndim == 1 || fused_starves(ndim, light, sources)) return false;
     int groups;
-    const int bpg = bins_per_group(ntiles, waves, nb, light, 0, &groups);
+    const int bpg = bins_per_group(ndim, ntiles, waves, nb, light, 0, &groups);
     const bool box = ndim == 3 && light;
     double fused = stage_cost(ntiles, waves, (light ? 1.1 : 1.2) * nb, box ? 1.6 : 1.3, box ? 0.51 : light ? 0.53 : 0.6);
     const long long load = ntiles * waves / 4;
