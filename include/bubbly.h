@@ -131,7 +131,9 @@ typedef struct bub_ctx bub_ctx;
 
 /* Create a context for one problem on the current HIP device.  Computes the bin
  * table on the host and allocates the context's device buffers
- * (about (ndim+6)*N*8 bytes).  *out receives the context (caller destroys it). */
+ * (about (ndim+6)*N*8 bytes; twice that where its stages can carry the primitive
+ * pass of the state they write: grids of 2^19 cells or more, 2D and 3D ones from
+ * 2^14 on, and one-bin problems).  *out receives the context (caller destroys it). */
 int bub_ctx_create(const bub_grid *grid, const bub_liquid *liq, const bub_gas *gas,
                    const bub_bins *bins, const bub_opts *opts, bub_ctx **out);
 
@@ -367,10 +369,11 @@ int bub_batch_destroy(bub_batch *batch);
 
 /* Add a member that needs `steps` more steps from bub_batch_run (0: open-ended,
  * stepped by every run and never reported done); *slot receives its handle.
- * BUB_ENOMEM if its bytes (3 state copies + bub_ctx_buffer_bytes) exceed what
- * the budget has left; BUB_EINVAL if the batch is full, steps < 0, the precision
- * differs, the context is already a member, or q and work overlap.  A member
- * whose (ndim, nb) class was autotuned gets that class's stage tile shape. */
+ * BUB_ENOMEM if its bytes (3 state copies and the context's buffers:
+ * bub_ctx_buffer_bytes, and (ndim+6)*N*8 more where a context of bub_ctx_create
+ * has a second primitive scratch below 2^19 cells) exceed what the budget has
+ * left; BUB_EINVAL if the batch is full, steps < 0, the precision differs, the
+ * context is already a member, or q and work overlap.  A member whose (ndim, nb) class was autotuned gets that class's stage tile shape. */
 int bub_batch_add(bub_batch *batch, bub_ctx *ctx, double *q, double *work, int steps, int *slot);
 /* Remove a member (its bytes return to the budget).  Its buffers must stay
  * valid until the work already enqueued for it has finished. */

@@ -558,6 +558,14 @@ void ctx_buffer_layout(int ndim, long long N, size_t *off_sc, size_t *off_P, siz
     *total = *off_P + pbytes + (*off_P2 ? pbytes : 0);
 }
 
+// Device bytes that a context holds (a context with memory of its own may have a second scratch below 2^19 cells too).
+size_t ctx_bytes(const bub_ctx *c)
+{
+    size_t off_sc, off_P, off_P2, total;
+    ctx_buffer_layout(c->ndim, c->N, &off_sc, &off_P, &off_P2, &total);
+    return off_P + (c->d_P2 ? 2 : 1) * align256(sizeof(double) * (size_t)c->nprim * (size_t)c->N);
+}
+
 void ctx_finish(bub_ctx *c)
 {
     c->bt.r0 = c->d_bins;
@@ -1679,9 +1687,7 @@ int bub_batch_add(bub_batch *b, bub_ctx *c, double *q, double *work, int steps, 
     if (!is_device_memory(q) || !is_device_memory(work) || !is_device_memory(c->d_P) ||
         !is_device_memory(c->d_sc) || !is_device_memory(c->d_bins))
         return BUB_EINVAL;
-    size_t off_sc, off_P, off_P2, ctx_bytes;
-    ctx_buffer_layout(c->ndim, c->N, &off_sc, &off_P, &off_P2, &ctx_bytes);
-    const size_t bytes = 3 * sizeof(double) * M + ctx_bytes;   // state, work, the context's buffers
+    const size_t bytes = 3 * sizeof(double) * M + ctx_bytes(c);   // state, work, the context's buffers
     if (b->budget && b->used_bytes + bytes > b->budget) return BUB_ENOMEM;
     for (size_t i = 0; i < b->slots.size(); ++i) {
         auto &m = b->slots[i];

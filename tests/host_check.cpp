@@ -1,0 +1,84 @@
+// Host-side checks of the library over a stand-in HIP runtime (fake_hip.hpp, no GPU use).  host_check NAME runs one
+// check; exit status 0 only if it holds.
+#include "fake_hip.hpp"
+
+#include "bubbly.h"
+
+static int failures = 0;
+#define CHECK(cond, ...)                       \
+    do {                                       \
+        if (!(cond)) {                         \
+            std::printf("%s: ", #cond);        \
+            std::printf(__VA_ARGS__);          \
+            std::printf("\n");                 \
+            ++failures;                        \
+        }                                      \
+    } while (0)
+
+struct Problem {
+    bub_grid grid{};
+    bub_liquid liq{7.1, 3.06e8, 1000.0, 101325.0};
+    bub_gas gas{1.4, 0.0728, 1e-3, 0.0};
+    bub_bins bins{5, 10e-6, 0.3};
+    bub_opts opts{};
+    Problem(int ndim, int nx, int ny, int nz, int nb)
+    {
+        grid.ndim = ndim;
+        const int n[3] = {nx, ny, nz};
+        for (int d = 0; d < 3; ++d) grid.n[d] = n[d], grid.dx[d] = 1e-4;
+        bins.nb = nb;
+        opts.cfl = 0.3;
+        opts.sub_rtol = 1e-4;
+        opts.max_substeps = 1000;
+        opts.transfer = {1.4, 287.06, 461.52, 293.15, 0.0257, 2.42e-5, 5.0, 5.0};
+    }
+    Problem &kappa(double k) { return gas.kappa = k, *this; }
+    Problem &mixed() { return opts.precision = BUB_PREC_MIXED, *this; }
+    Problem &split() { return opts.bubble_mode = BUB_BUBBLES_SPLIT, *this; }
+    Problem &viscous() { return opts.viscous = 1, *this; }
+    Problem &transfer() { return opts.contents = BUB_CONTENTS_TRANSFER, *this; }
+    bub_ctx *make() const
+    {
+        bub_ctx *c = nullptr;
+        const int rc = bub_ctx_create(&grid, &liq, &gas, &bins, &opts, &c);
+        CHECK(rc == BUB_OK, "bub_ctx_create: %d", rc);
+        return c;
+    }
+};
+
+static double *pretend(size_t at) { return (double *)(at << 40); }   // a device address that nothing reads
+
+// A batch charges a member the device bytes that it holds: state, work, and what its context allocated.
+static void budget()
+{
+    Problem all[] = {Problem(2, 200, 200, 1, 5), Problem(2, 200, 200, 1, 1), Problem(3, 40, 40, 40, 11), Problem(1, 400, 1, 1, 11),
+                     Problem(2, 70, 37, 1, 5), Problem(2, 800, 700, 1, 3), Problem(2, 200, 200, 1, 5).kappa(5.0 / 3.0),
+                     Problem(2, 300, 200, 1, 5).transfer()};
+    for (const Problem &p : all) {
+        const size_t before = fake().held();
+        bub_ctx *c = p.make();
+        const size_t ctx = fake().held() - before;
+        size_t sb;
+        bub_layout(c, nullptr, nullptr, nullptr, &sb, nullptr);
+        const size_t need = 3 * sb + ctx;
+        int slot;
+        for (int fits = 0; fits < 2; ++fits) {   // (the parts of a context's buffers are counted in units of 256)
+            bub_batch *b = nullptr;
+            CHECK(bub_batch_create(BUB_PREC_FP64, 2, fits ? need + 1024 : need - 1, &b) == BUB_OK, "batch");
+            const int rc = bub_batch_add(b, c, pretend(1), pretend(2), 1, &slot);
+            CHECK(rc == (fits ? BUB_OK : BUB_ENOMEM), "%dD %d x %d x %d, %d bins, kappa %g: %d (holds %zu)", p.grid.ndim,
+                  p.grid.n[0], p.grid.n[1], p.grid.n[2], p.bins.nb, p.gas.kappa, rc, need);
+            bub_batch_destroy(b);
+        }
+        bub_ctx_destroy(c);
+    }
+}
+
+int main(int argc, char **argv)
+{
+    const std::string name = argc > 1 ? argv[1] : "";
+    if (name == "budget") budget();
+    else return 2;
+    std::printf("%d failures\n", failures);
+    return failures != 0;
+}
