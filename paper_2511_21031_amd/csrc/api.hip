@@ -723,12 +723,19 @@ int bub_ctx_create(const bub_grid *grid, const bub_liquid *liq, const bub_gas *g
     // allocation of its own takes some 75 us)
     const size_t p2 = align256(pbytes);
     const bool two = slots_for(c->N, c->nb) == 1 || (c->ndim > 1 && c->N >= FUSE_CELLS && !c->opts.viscous && ct_of(c) != CT_POLY);
-    if (hipMalloc(&c->d_bins, sizeof(double) * BIN_FIELDS * NB_MAX) != hipSuccess ||
-        hipMalloc(&c->d_P, two ? 2 * p2 : pbytes) != hipSuccess || hipMalloc(&c->d_sc, sizeof(Scalars)) != hipSuccess) {
+    if (two && hipMalloc(&c->d_P, 2 * p2) == hipSuccess) {
+        c->d_P2 = c->d_P + p2 / sizeof(double);
+    } else {   // (one scratch is enough to run: the stages then take separate passes)
+        (void)hipGetLastError();
+        c->d_P = nullptr;
+        if (hipMalloc(&c->d_P, pbytes) != hipSuccess) c->d_P = nullptr;
+    }
+    if (!c->d_P || hipMalloc(&c->d_bins, sizeof(double) * BIN_FIELDS * NB_MAX) != hipSuccess ||
+        hipMalloc(&c->d_sc, sizeof(Scalars)) != hipSuccess) {
+        (void)hipGetLastError();   // (not the next launch's)
         bub_ctx_destroy(c);
         return BUB_ENOMEM;
     }
-    if (two) c->d_P2 = c->d_P + p2 / sizeof(double);
     double tab[BIN_FIELDS * NB_MAX];
     bin_table(c, tab);
     Scalars zero{};

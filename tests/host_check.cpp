@@ -74,10 +74,36 @@ static void budget()
     }
 }
 
+// Where the device has room for one primitive scratch but not for two, a context runs with one; a failed attempt leaves
+// no error behind for the launches that follow.
+static void scratch()
+{
+    Problem all[] = {Problem(2, 200, 200, 1, 5), Problem(3, 40, 40, 40, 11), Problem(2, 800, 700, 1, 3), Problem(2, 30, 20, 1, 1)};
+    for (const Problem &p : all) {
+        const size_t one = 8 * (size_t)(p.grid.ndim + 6) * p.grid.n[0] * p.grid.n[1] * p.grid.n[2];
+        fake().limit = one + 4096 > 16384 ? one + 4096 : 16384;
+        bub_ctx *c = p.make();
+        if (c) {
+            CHECK(bub_rk3_steps(c, pretend(1), pretend(2), 2, 0.0, nullptr, nullptr) == BUB_OK, "steps");
+            bub_ctx_destroy(c);
+        }
+        fake().limit = one / 2;   // not even one
+        bub_ctx *none = nullptr;
+        if (one / 2 > 16384)
+            CHECK(bub_ctx_create(&p.grid, &p.liq, &p.gas, &p.bins, &p.opts, &none) == BUB_ENOMEM && !none, "no room");
+        CHECK(fake().mem.empty(), "%zu bytes left behind", fake().held());
+        fake().limit = ~(size_t)0;
+        bub_ctx *c2 = p.make();
+        CHECK(bub_rk3_steps(c2, pretend(1), pretend(2), 2, 0.0, nullptr, nullptr) == BUB_OK, "steps after a refusal");
+        bub_ctx_destroy(c2);
+    }
+}
+
 int main(int argc, char **argv)
 {
     const std::string name = argc > 1 ? argv[1] : "";
     if (name == "budget") budget();
+    else if (name == "scratch") scratch();
     else return 2;
     std::printf("%d failures\n", failures);
     return failures != 0;
