@@ -456,6 +456,17 @@ long long stage_tiles(const bub_ctx *c, int *waves)
 // Cells from which a context that allocates its own memory keeps the second primitive scratch.
 constexpr long long FUSE_CELLS = 1 << 14;
 
+// Whether stages of the context can ever carry the primitive pass, whatever its shape and groups are set to.
+bool wants_two_scratches(const bub_ctx *c)
+{
+    if (c->opts.viscous || ct_of(c) == CT_POLY) return false;
+    const bool light = c->opts.precision == BUB_PREC_MIXED;
+    if (c->ndim == 3 && !light && ct_air(c) != CT_AIR) return false;
+    if (slots_for(c->N, c->nb) == 1) return true;
+    return c->ndim > 1 && c->N >= FUSE_CELLS && tile_ok(c, kernel_shape(c)) &&
+           !fused_starves(c->ndim, light, c->opts.bubble_mode == BUB_BUBBLES_UNSPLIT);
+}
+
 // The stage kernels can carry the primitive pass of the state they write (fused epilogue) when one
 // workgroup owns all bins of a tile.  The tile kernels sum the bins in the order of the grid's primitive
 // pass, the others only in that of one thread per cell, so results are bitwise those of separate passes.
@@ -722,7 +733,7 @@ int bub_ctx_create(const bub_grid *grid, const bub_liquid *liq, const bub_gas *g
     // the second primitive scratch, where stages can carry the pass, is the rest of the first one's allocation (an
     // allocation of its own takes some 75 us)
     const size_t p2 = align256(pbytes);
-    const bool two = slots_for(c->N, c->nb) == 1 || (c->ndim > 1 && c->N >= FUSE_CELLS && !c->opts.viscous && ct_of(c) != CT_POLY);
+    const bool two = wants_two_scratches(c);
     if (two && hipMalloc(&c->d_P, 2 * p2) == hipSuccess) {
         c->d_P2 = c->d_P + p2 / sizeof(double);
     } else {   // (one scratch is enough to run: the stages then take separate passes)

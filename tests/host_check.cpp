@@ -99,11 +99,36 @@ static void scratch()
     }
 }
 
+// A second scratch is held only where a stage can ever use it.
+static void unused()
+{
+    struct { Problem p; int scratches; } all[] = {
+        {Problem(2, 200, 200, 1, 5), 2}, {Problem(2, 200, 200, 1, 5).split(), 2}, {Problem(3, 40, 40, 40, 11), 2},
+        {Problem(3, 40, 40, 40, 11).mixed().split(), 2}, {Problem(2, 200, 200, 1, 5).transfer(), 2},
+        {Problem(2, 800, 700, 1, 3).kappa(5.0 / 3.0), 2}, {Problem(1, 600000, 1, 1, 3), 2}, {Problem(3, 90, 90, 90, 3).mixed(), 2},
+        {Problem(1, 4000, 1, 1, 11), 1}, {Problem(2, 100, 100, 1, 5), 1},
+        {Problem(2, 200, 200, 1, 5).kappa(5.0 / 3.0), 1},   // no tile kernel below 2^19 cells
+        {Problem(2, 200, 200, 1, 5).kappa(1.35), 1}, {Problem(2, 800, 700, 1, 3).kappa(1.35), 1},
+        {Problem(2, 200, 200, 1, 5).viscous(), 1}, {Problem(2, 800, 700, 1, 3).viscous(), 1}, {Problem(1, 4000, 1, 1, 1).viscous(), 1},
+        {Problem(3, 40, 40, 40, 11).mixed(), 1}, {Problem(3, 40, 40, 40, 11).transfer(), 1},
+    };
+    for (auto &a : all) {
+        const size_t before = fake().held();
+        bub_ctx *c = a.p.make();
+        const size_t one = 8 * (size_t)(a.p.grid.ndim + 6) * a.p.grid.n[0] * a.p.grid.n[1] * a.p.grid.n[2];
+        const double held = (double)(fake().held() - before) / one;   // (and some 11 KB of tables)
+        CHECK((int)(held + 0.01) == a.scratches, "%dD %d x %d x %d, kappa %g: holds %g scratches, not %d", a.p.grid.ndim,
+              a.p.grid.n[0], a.p.grid.n[1], a.p.grid.n[2], a.p.gas.kappa, held, a.scratches);
+        bub_ctx_destroy(c);
+    }
+}
+
 int main(int argc, char **argv)
 {
     const std::string name = argc > 1 ? argv[1] : "";
     if (name == "budget") budget();
     else if (name == "scratch") scratch();
+    else if (name == "unused") unused();
     else return 2;
     std::printf("%d failures\n", failures);
     return failures != 0;
