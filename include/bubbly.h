@@ -416,7 +416,8 @@ int bub_batch_graphs(bub_batch *batch, int enable);
 /* Members, total cells and total cell-bins of the current members. */
 int bub_batch_info(const bub_batch *batch, int *ncases, int64_t *cells, int64_t *cell_bins);
 
-/* Autotuner of the stage kernel's tile shape per (ndim, nb) class: for every
+/* Autotuner of the stage kernel's tile shape per class of (ndim, nb), polytropic
+ * air apart from the other gases, whose kernels differ: for every
  * member whose class has no tuned shape yet, bub_autotune on that member (its
  * work buffer receives right-hand sides; its state is not changed) picks the
  * fastest shape, which then applies to every member of the class, present and
@@ -476,13 +477,14 @@ int bub_autotune(bub_ctx *ctx, const double *q, double *scratch, int reps, doubl
 
 /* The autotuner with a cache of its choices that persists across processes:
  * a text file (created on the first store) of lines
- * "<arch> <ndim> <nb> <precision> <size class> <tile>", keyed by the GPU's
- * architecture name (e.g. gfx950), the context's dimensionality, bin count
+ * "<kernels> <ndim> <nb> <precision> <size class> <tile>", keyed by the GPU's
+ * architecture name (e.g. gfx950; gfx950/air for polytropic air, whose shapes
+ * have kernels of their own), the context's dimensionality, bin count
  * and precision, and floor(log2 N).  With an entry for the context's key the
  * context takes that tile shape at once (*hit = 1; no launch, no
  * synchronisation, q and scratch unused); otherwise bub_autotune runs and its
  * choice is appended to the file (*hit = 0).  Lines that do not parse or name
- * no valid shape are ignored; the last matching line wins.  best and hit may
+ * no shape that the context can run are ignored; the last matching line wins.  best and hit may
  * be NULL.  BUB_EINVAL if the file cannot be appended to. */
 int bub_autotune_cached(bub_ctx *ctx, const char *cache_path, const double *q, double *scratch, int reps,
                         int *best, int *hit, void *stream);

@@ -153,12 +153,14 @@ int air_shape(const bub_ctx *c)
 }
 int shape_of(const bub_ctx *c)
 {
-    // (a batch applies one shape to a whole class, whose members need not all have it)
-    if (c->tile >= 0 && !(c->ndim == 1 && c->tile == LINE_SHAPE && !line_ok(c))) return c->tile;
+    if (c->tile >= 0) return c->tile;
     if (!pw_fast(c)) return 0;
     const int v = air_shape(c);
     return (c->ndim == 1 ? line_ok(c) : tile_ok(c, v)) ? v : 0;
 }
+
+// Shapes of the list that a fifth-root power can run (the wave tiles are air's).
+int shapes_usable(const bub_ctx *c) { return TILE_COUNT[c->ndim] - (c->ndim == 1 && !line_ok(c)); }
 
 // The shape whose kernel its stages run (transfer contents, listed with shape 0 only, have one of their own).
 int kernel_shape(const bub_ctx *c) { return ct_of(c) == CT_TRANSFER ? air_shape(c) : pw_fast(c) ? shape_of(c) : 0; }
@@ -1329,9 +1331,11 @@ int bub_tile_get(const bub_ctx *c, int *idx)
 
 namespace {
 
-// Tile-shape cache: a text file of lines "<arch> <ndim> <nb> <precision> <size class> <tile>", the size
-// class being floor(log2 N).  Lines that do not parse, or name another shape count, are ignored; the
-// last matching line wins.
+// Tile-shape cache: a text file of lines "<kernels> <ndim> <nb> <precision> <size class> <tile>", the size
+// class being floor(log2 N).  <kernels> names the architecture and, where shapes have kernels of their own, whose:
+// "gfx950/air" for polytropic air (line_kernel.hpp, tile_kernel.hpp), "gfx950" for the other fifth-root powers, whose
+// shapes all run stage_kernel.hpp, as air's did where an older file has "gfx950" lines of it.  Lines that do not parse,
+// or name a shape that the context cannot run, are ignored; the last matching line wins.
 struct TuneKey {
     char arch[64];
     int ndim, nb, precision, size_class;
@@ -1346,6 +1350,7 @@ int tune_key(const bub_ctx *c, TuneKey *k)
                     prop.gcnArchName[i] != ' ';
          ++i)
         k->arch[i] = prop.gcnArchName[i];
+    if (ct_air(c) == CT_AIR) std::strncat(k->arch, "/air", sizeof(k->arch) - 1 - std::strlen(k->arch));
     k->ndim = c->ndim;
     k->nb = c->nb;
     k->precision = c->opts.precision;
@@ -1397,7 +1402,7 @@ int bub_autotune_cached(bub_ctx *c, const char *cache_path, const double *q, dou
     TuneKey k;
     int rc = tune_key(c, &k);
     if (rc) return rc;
-    const int t = tune_lookup(cache_path, k, TILE_COUNT[c->ndim]);
+    const int t = tune_lookup(cache_path, k, shapes_usable(c));
     if (hit) *hit = t >= 0;
     if (t >= 0) {
         c->tile = t;
@@ -1430,7 +1435,7 @@ int bub_autotune(bub_ctx *c, const double *q, double *scratch, int reps, double 
     c->prof_on = 0;
     double best_ms = 1e300;
     int best_v = keep;
-    const int nshape = !pw_fast(c) ? 1 : TILE_COUNT[c->ndim] - (c->ndim == 1 && !line_ok(c));
+    const int nshape = pw_fast(c) ? shapes_usable(c) : 1;
     if (ms_out)
         for (int v = nshape; v < TILE_COUNT[c->ndim]; ++v) ms_out[v] = -1.0;
     for (int v = 0; v < nshape && rc == BUB_OK; ++v) {
@@ -1543,8 +1548,12 @@ struct bub_batch {
     hipStream_t st[NSTREAM] = {};
     hipEvent_t fork = nullptr;
     hipEvent_t join[NSTREAM] = {};
-    std::vector<std::pair<int, int>> tuned_key;   // (ndim, nb) classes with an autotuned tile
-    std::vector<int> tuned_tile;
+    struct Class {
+        int ndim, nb;
+        bool air;   // (its shapes have kernels of their own)
+        int tile;
+    };
+    std::vector<Class> tuned;                     // classes with an autotuned tile
     std::string tune_cache;                       // tile-shape cache file of the class autotuner ("" = none)
 };
 
@@ -1571,8 +1580,8 @@ bool is_device_memory(const void *p)
 
 int batch_class_tile(const bub_batch *b, const bub_ctx *c)
 {
-    for (size_t i = 0; i < b->tuned_key.size(); ++i)
-        if (b->tuned_key[i].first == c->ndim && b->tuned_key[i].second == c->nb) return b->tuned_tile[i];
+    for (const auto &k : b->tuned)
+        if (k.ndim == c->ndim && k.nb == c->nb && k.air == (ct_air(c) == CT_AIR)) return k.tile;
     return -1;
 }
 
@@ -1853,7 +1862,6 @@ int bub_batch_autotune(bub_batch *b, int reps, int *classes, void *stream)
 {
     if (!b || reps < 1) return BUB_EINVAL;
     hipStream_t s = (hipStream_t)stream;
-    int tuned = 0;
     for (size_t i = 0; i < b->slots.size(); ++i) {
         auto &m = b->slots[i];
         if (!m.used || !pw_fast(m.ctx)) continue;   // the general power has one stage shape
@@ -1865,15 +1873,12 @@ int bub_batch_autotune(bub_batch *b, int reps, int *classes, void *stream)
                          ? bub_autotune(m.ctx, m.q, m.work, reps, nullptr, &t, s)
                          : bub_autotune_cached(m.ctx, b->tune_cache.c_str(), m.q, m.work, reps, &t, nullptr, s);
             if (rc) return rc;
-            b->tuned_key.emplace_back(m.ctx->ndim, m.ctx->nb);
-            b->tuned_tile.push_back(t);
-            ++tuned;
+            b->tuned.push_back({m.ctx->ndim, m.ctx->nb, ct_air(m.ctx) == CT_AIR, t});
         }
         m.ctx->tile = t;
     }
     b->dirty = true;   // stage decompositions of the grouped launches follow the tiles
-    if (classes) *classes = (int)b->tuned_key.size();
-    (void)tuned;
+    if (classes) *classes = (int)b->tuned.size();
     return BUB_OK;
 }
 

@@ -87,7 +87,7 @@ class Server:
         self.used = 0
         self.peak_used = 0
         self.peak_active = 0
-        self.classes = set()      # (ndim, nb) classes seen; a new one triggers the batch autotuner
+        self.classes = set()      # (ndim, nb, kappa) seen; new ones trigger the batch autotuner (air is a class of its own)
         self._tune = False
         self.chunks = []          # (member request ids, steps) of every batched step call
         self._setup()
@@ -119,7 +119,7 @@ class Server:
             q = ctx.init_state(prim, stream=self.stream)
             work = ctx.new_work()
         rec._keep = (ctx, q, work, prim, host)
-        key = (case.ndim, case.nb)
+        key = (case.ndim, case.nb, case.gas["kappa"])
         if key not in self.classes:
             self.classes.add(key)
             self._tune = True
@@ -127,7 +127,7 @@ class Server:
 
     def _step(self, nsteps: int, nactive: int):
         if self.autotune and self._tune:
-            # tile shape of each new (ndim, nb) class (synchronises the server stream once per class)
+            # tile shape of each new class (synchronises the server stream once per class)
             self.batch.autotune(reps=2, stream=self.stream)
             self._tune = False
         if self.use_run:

@@ -123,12 +123,72 @@ static void unused()
     }
 }
 
+// The tile-shape cache keeps polytropic air, whose shapes have kernels of their own, apart from other gases: a hit is a
+// shape that the context runs and reports.  (The stand-in clock makes the last shape that is timed the fastest.)
+static void cache()
+{
+    auto put = [](const char *text) {
+        std::FILE *f = std::fopen("tiles.txt", "w");
+        std::fputs(text, f);
+        std::fclose(f);
+    };
+    auto tuned = [](const Problem &p, int want_hit, int want) {
+        bub_ctx *c = p.make();
+        int best = -1, hit = -1, get = -1;
+        const int rc = bub_autotune_cached(c, "tiles.txt", pretend(1), pretend(2), 1, &best, &hit, nullptr);
+        bub_tile_get(c, &get);
+        CHECK(rc == BUB_OK && hit == want_hit && best == want && get == want, "kappa %g: %d, hit %d, best %d, tile %d; not %d %d",
+              p.gas.kappa, rc, hit, best, get, want_hit, want);
+        bub_ctx_destroy(c);
+    };
+    const Problem air(1, 400, 1, 1, 11), other = Problem(1, 400, 1, 1, 11).kappa(5.0 / 3.0);
+    put("");
+    tuned(air, 0, 3);     // one wave a tile, air's only
+    tuned(other, 0, 2);
+    tuned(air, 1, 3);
+    tuned(other, 1, 2);
+    put("gfx950 1 11 0 8 1\n");   // of a file from before air had kernels of its own
+    tuned(other, 1, 1);
+    tuned(air, 0, 3);
+    put("gfx950 1 11 0 8 3\n");   // a shape that the context cannot run
+    tuned(other, 0, 2);
+    const Problem air2(2, 70, 37, 1, 5), other2 = Problem(2, 70, 37, 1, 5).kappa(1.0);
+    put("gfx950 2 5 0 11 0\n");
+    tuned(air2, 0, 5);
+    tuned(other2, 1, 0);
+}
+
+// So does the class autotuner of a batch, for members present and later ones.
+static void classes()
+{
+    bub_batch *b = nullptr;
+    CHECK(bub_batch_create(BUB_PREC_FP64, 4, 0, &b) == BUB_OK, "batch");
+    const Problem ps[] = {Problem(1, 400, 1, 1, 11), Problem(1, 300, 1, 1, 11).kappa(5.0 / 3.0), Problem(1, 350, 1, 1, 11).kappa(5.0 / 3.0),
+                          Problem(1, 500, 1, 1, 11)};
+    const int want[] = {3, 2, 2, 3};
+    bub_ctx *c[4];
+    int slot, n = 0, get;
+    for (int i = 0; i < 4; ++i) {
+        c[i] = ps[i].make();
+        CHECK(bub_batch_add(b, c[i], pretend(2 * i + 1), pretend(2 * i + 2), 0, &slot) == BUB_OK, "add");
+        if (i == 1) CHECK(bub_batch_autotune(b, 1, &n, nullptr) == BUB_OK && n == 2, "%d classes", n);
+    }
+    for (int i = 0; i < 4; ++i) {
+        bub_tile_get(c[i], &get);
+        CHECK(get == want[i], "member %d: shape %d", i, get);
+    }
+    bub_batch_destroy(b);
+    for (bub_ctx *x : c) bub_ctx_destroy(x);
+}
+
 int main(int argc, char **argv)
 {
     const std::string name = argc > 1 ? argv[1] : "";
     if (name == "budget") budget();
     else if (name == "scratch") scratch();
     else if (name == "unused") unused();
+    else if (name == "cache") cache();
+    else if (name == "classes") classes();
     else return 2;
     std::printf("%d failures\n", failures);
     return failures != 0;
