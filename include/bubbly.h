@@ -373,7 +373,8 @@ int bub_batch_destroy(bub_batch *batch);
  * bub_ctx_buffer_bytes, and (ndim+6)*N*8 more where a context of bub_ctx_create
  * has a second primitive scratch below 2^19 cells) exceed what the budget has
  * left; BUB_EINVAL if the batch is full, steps < 0, the precision differs, the
- * context is already a member, or q and work overlap.  A member whose (ndim, nb) class was autotuned gets that class's stage tile shape. */
+ * context is already a member, or q and work overlap.  A member whose class
+ * (bub_batch_autotune) was tuned gets that class's stage tile shape. */
 int bub_batch_add(bub_batch *batch, bub_ctx *ctx, double *q, double *work, int steps, int *slot);
 /* Remove a member (its bytes return to the budget).  Its buffers must stay
  * valid until the work already enqueued for it has finished. */

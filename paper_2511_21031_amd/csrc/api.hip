@@ -127,6 +127,27 @@ void tile_info(int *tx, int *ty, int *tz, int *block)
     *block = Tile<D, V>::BLOCK;
 }
 
+void shape_info(int ndim, int idx, int *tx, int *ty, int *tz, int *block)
+{
+    switch (ndim * 10 + idx) {
+    case 10: tile_info<1, 0>(tx, ty, tz, block); break;
+    case 11: tile_info<1, 1>(tx, ty, tz, block); break;
+    case 12: tile_info<1, 2>(tx, ty, tz, block); break;
+    case 10 + LINE_SHAPE: *tx = 63, *ty = *tz = 1, *block = 64; break;
+    case 20: tile_info<2, 0>(tx, ty, tz, block); break;
+    case 21: tile_info<2, 1>(tx, ty, tz, block); break;
+    case 22: tile_info<2, 2>(tx, ty, tz, block); break;
+    case 23: tile_info<2, 3>(tx, ty, tz, block); break;
+    case 24: tile_info<2, 4>(tx, ty, tz, block); break;
+    case 25: tile_info<2, 5>(tx, ty, tz, block); break;
+    case 30: tile_info<3, 0>(tx, ty, tz, block); break;
+    case 31: tile_info<3, 1>(tx, ty, tz, block); break;
+    case 32: tile_info<3, 2>(tx, ty, tz, block); break;
+    case 33: tile_info<3, 3>(tx, ty, tz, block); break;
+    default: tile_info<3, 4>(tx, ty, tz, block); break;
+    }
+}
+
 // The kernels are compiled for the bubble contents (Contents): polytropic gas whose power x^(3 kappa)
 // takes the fifth-root Newton form when 3 kappa is a whole number of fifths (air's 4.2, 3, 5, ...) or the
 // general exp2(3 kappa log2 x) form otherwise, or transfer contents.  Only the fifth-root form has every
@@ -159,8 +180,8 @@ int shape_of(const bub_ctx *c)
     return (c->ndim == 1 ? line_ok(c) : tile_ok(c, v)) ? v : 0;
 }
 
-// Shapes of the list that a fifth-root power can run (the wave tiles are air's).
-int shapes_usable(const bub_ctx *c) { return TILE_COUNT[c->ndim] - (c->ndim == 1 && !line_ok(c)); }
+// Shapes that are listed for a context: the wave tiles of 1D for air only, whose stages alone can be set to them.
+int shapes_listed(const bub_ctx *c) { return TILE_COUNT[c->ndim] - (c->ndim == 1 && !(pw_fast(c) && line_ok(c))); }
 
 // The shape whose kernel its stages run (transfer contents, listed with shape 0 only, have one of their own).
 int kernel_shape(const bub_ctx *c) { return ct_of(c) == CT_TRANSFER ? air_shape(c) : pw_fast(c) ? shape_of(c) : 0; }
@@ -450,7 +471,7 @@ int stage(bub_ctx *c, const StageArgs &A, hipStream_t s, double tc)
 long long stage_tiles(const bub_ctx *c, int *waves)
 {
     int tx, ty, tz, blk;
-    bub_tile_info(c, kernel_shape(c), &tx, &ty, &tz, &blk);
+    shape_info(c->ndim, kernel_shape(c), &tx, &ty, &tz, &blk);
     *waves = blk / 64;
     return (long long)((c->g.n[0] + tx - 1) / tx) * ((c->g.n[1] + ty - 1) / ty) * ((c->g.n[2] + tz - 1) / tz);
 }
@@ -1284,38 +1305,21 @@ int bub_bin_groups(bub_ctx *c, int groups)
 int bub_tile_count(const bub_ctx *c, int *count)
 {
     if (!c || !count) return BUB_EINVAL;
-    *count = TILE_COUNT[c->ndim];
+    *count = shapes_listed(c);
     return BUB_OK;
 }
 
 int bub_tile_info(const bub_ctx *c, int idx, int *tx, int *ty, int *tz, int *block)
 {
-    if (!c || !tx || !ty || !tz || !block || idx < 0 || idx >= TILE_COUNT[c->ndim]) return BUB_EINVAL;
-    switch (c->ndim * 10 + idx) {
-    case 10: tile_info<1, 0>(tx, ty, tz, block); break;
-    case 11: tile_info<1, 1>(tx, ty, tz, block); break;
-    case 12: tile_info<1, 2>(tx, ty, tz, block); break;
-    case 10 + LINE_SHAPE: *tx = 63, *ty = *tz = 1, *block = 64; break;
-    case 20: tile_info<2, 0>(tx, ty, tz, block); break;
-    case 21: tile_info<2, 1>(tx, ty, tz, block); break;
-    case 22: tile_info<2, 2>(tx, ty, tz, block); break;
-    case 23: tile_info<2, 3>(tx, ty, tz, block); break;
-    case 24: tile_info<2, 4>(tx, ty, tz, block); break;
-    case 25: tile_info<2, 5>(tx, ty, tz, block); break;
-    case 30: tile_info<3, 0>(tx, ty, tz, block); break;
-    case 31: tile_info<3, 1>(tx, ty, tz, block); break;
-    case 32: tile_info<3, 2>(tx, ty, tz, block); break;
-    case 33: tile_info<3, 3>(tx, ty, tz, block); break;
-    default: tile_info<3, 4>(tx, ty, tz, block); break;
-    }
+    if (!c || !tx || !ty || !tz || !block || idx < 0 || idx >= shapes_listed(c)) return BUB_EINVAL;
+    shape_info(c->ndim, idx, tx, ty, tz, block);
     return BUB_OK;
 }
 
 int bub_tile_set(bub_ctx *c, int idx)
 {
-    if (!c || idx < 0 || idx >= TILE_COUNT[c->ndim]) return BUB_EINVAL;
+    if (!c || idx < 0 || idx >= shapes_listed(c)) return BUB_EINVAL;
     if (idx != 0 && !pw_fast(c)) return BUB_EUNSUPPORTED;
-    if (c->ndim == 1 && idx == LINE_SHAPE && !line_ok(c)) return BUB_EUNSUPPORTED;
     c->tile = idx;
     return BUB_OK;
 }
@@ -1402,7 +1406,7 @@ int bub_autotune_cached(bub_ctx *c, const char *cache_path, const double *q, dou
     TuneKey k;
     int rc = tune_key(c, &k);
     if (rc) return rc;
-    const int t = tune_lookup(cache_path, k, shapes_usable(c));
+    const int t = tune_lookup(cache_path, k, shapes_listed(c));
     if (hit) *hit = t >= 0;
     if (t >= 0) {
         c->tile = t;
@@ -1435,9 +1439,9 @@ int bub_autotune(bub_ctx *c, const double *q, double *scratch, int reps, double 
     c->prof_on = 0;
     double best_ms = 1e300;
     int best_v = keep;
-    const int nshape = pw_fast(c) ? shapes_usable(c) : 1;
+    const int nlist = shapes_listed(c), nshape = pw_fast(c) ? nlist : 1;
     if (ms_out)
-        for (int v = nshape; v < TILE_COUNT[c->ndim]; ++v) ms_out[v] = -1.0;
+        for (int v = nshape; v < nlist; ++v) ms_out[v] = -1.0;
     for (int v = 0; v < nshape && rc == BUB_OK; ++v) {
         c->tile = v;
         rc = stage_kernel(c, A, s);  // warm-up (code load)
@@ -1981,7 +1985,7 @@ int member_desc(const bub_batch::Member &m, BatchMember *d)
     d->max_substeps = c->opts.max_substeps > 0 ? c->opts.max_substeps : 10000;
     d->sources = c->opts.bubble_mode == BUB_BUBBLES_UNSPLIT;
     int tx, ty, tz, blk;
-    if (bub_tile_info(c, shape_of(c), &tx, &ty, &tz, &blk)) return BUB_EINVAL;
+    shape_info(c->ndim, shape_of(c), &tx, &ty, &tz, &blk);
     d->ntile[0] = (c->g.n[0] + tx - 1) / tx;
     d->ntile[1] = (c->g.n[1] + ty - 1) / ty;
     d->ntile[2] = (c->g.n[2] + tz - 1) / tz;

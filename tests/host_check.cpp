@@ -181,6 +181,40 @@ static void classes()
     for (bub_ctx *x : c) bub_ctx_destroy(x);
 }
 
+// Every shape that is listed for a polytropic gas with a fifth-root power can be set, is reported and runs; the autotuner
+// writes no more times than shapes are listed.
+static void shapes()
+{
+    for (double kappa : {1.4, 5.0 / 3.0, 1.0, 1.35})
+        for (int ndim = 1; ndim <= 3; ++ndim) {
+            Problem p = ndim == 1 ? Problem(1, 400, 1, 1, 11) : ndim == 2 ? Problem(2, 70, 37, 1, 5) : Problem(3, 20, 13, 11, 3);
+            bub_ctx *c = p.kappa(kappa).make();
+            int n = 0;
+            CHECK(bub_tile_count(c, &n) == BUB_OK, "count");
+            const int want[] = {0, kappa == 1.4 ? 4 : 3, 6, 5};
+            CHECK(n == want[ndim], "%dD, kappa %g: %d shapes", ndim, kappa, n);
+            for (int i = 0; i < n; ++i) {
+                int t[4], get = -1;
+                CHECK(bub_tile_info(c, i, &t[0], &t[1], &t[2], &t[3]) == BUB_OK, "info %d", i);
+                const int rc = bub_tile_set(c, i);
+                if (kappa == 1.35 && i) {   // the general power has one shape
+                    CHECK(rc == BUB_EUNSUPPORTED, "set %d: %d", i, rc);
+                    continue;
+                }
+                CHECK(rc == BUB_OK && bub_tile_get(c, &get) == BUB_OK && get == i, "%dD, kappa %g: set %d: %d, then %d", ndim,
+                      kappa, i, rc, get);
+                CHECK(bub_rhs_stage(c, pretend(1), pretend(2), nullptr) == BUB_OK, "rhs");
+                CHECK(fake().launches.back().block.x == (unsigned)t[3], "%dD, kappa %g, shape %d: %u threads, listed %d", ndim,
+                      kappa, i, fake().launches.back().block.x, t[3]);
+            }
+            CHECK(bub_tile_set(c, n) == BUB_EINVAL, "a shape past the list");
+            double ms[8] = {7, 7, 7, 7, 7, 7, 7, 7};
+            CHECK(bub_autotune(c, pretend(1), pretend(2), 1, ms, nullptr, nullptr) == BUB_OK, "autotune");
+            for (int i = 0; i < 8; ++i) CHECK((ms[i] != 7) == (i < n), "%dD, kappa %g: time %d", ndim, kappa, i);
+            bub_ctx_destroy(c);
+        }
+}
+
 int main(int argc, char **argv)
 {
     const std::string name = argc > 1 ? argv[1] : "";
@@ -188,6 +222,7 @@ int main(int argc, char **argv)
     else if (name == "scratch") scratch();
     else if (name == "unused") unused();
     else if (name == "cache") cache();
+    else if (name == "shapes") shapes();
     else if (name == "classes") classes();
     else return 2;
     std::printf("%d failures\n", failures);
