@@ -92,7 +92,7 @@ typedef struct { int nb; double r0_median, sigma_ln; } bub_bins;
  * dp_b/dt = 3 gam_b/R (-Rdot p_b + Rv T0 dm_v/dt/(4 pi R^2) + (gam_b - 1)/gam_b k_b dT/dr).  At
  * equilibrium p_b0 = p0 + 2 sigma/R0 and m_v0 = pv V0/(Rv T0).  The paper does not give the
  * coefficients: the caller does.  Ensemble-averaged model only (the Lagrangian calls return
- * BUB_EUNSUPPORTED); stage shape 0 with the separate primitive pass.  gam_b: specific-heat ratio of
+ * BUB_EUNSUPPORTED); one stage shape, listed as 0.  gam_b: specific-heat ratio of
  * the contents; Rg, Rv: gas constants of gas and vapour (J/(kg K)); T0: liquid temperature (K);
  * k_b: thermal conductivity of the contents (W/(m K)); D_v: vapour-gas diffusion coefficient
  * (m^2/s); beta_T, beta_c: the transfer coefficients (>= 0). */
@@ -448,8 +448,10 @@ const char *bub_strerror(int code);
 /* Tile shapes of the fused stage kernel.  Each dimensionality has a fixed list
  * of compiled shapes (tile extent tx*ty*tz cells, `block` threads); a context
  * starts on the one its dimensionality, precision and contents usually do best
- * with (shape 0 for the general polytropic power).  Results do not depend on the shape (each face flux is
- * computed by the same arithmetic whichever tile owns it); only speed does.
+ * with (shape 0 for the general polytropic power and for transfer contents, which
+ * run that one only; the last 1D shape is listed for polytropic air alone).
+ * Results do not depend on the shape (each face flux is computed by the same
+ * arithmetic whichever tile owns it); only speed does.
  * bub_tile_info: shape idx of this context's dimensionality (host outputs).
  * bub_tile_set / bub_tile_get: select / query the shape used by later calls. */
 int bub_tile_count(const bub_ctx *ctx, int *count);

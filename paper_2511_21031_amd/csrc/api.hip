@@ -1312,7 +1312,8 @@ int bub_tile_count(const bub_ctx *c, int *count)
 int bub_tile_info(const bub_ctx *c, int idx, int *tx, int *ty, int *tz, int *block)
 {
     if (!c || !tx || !ty || !tz || !block || idx < 0 || idx >= shapes_listed(c)) return BUB_EINVAL;
-    shape_info(c->ndim, idx, tx, ty, tz, block);
+    // transfer contents run one shape, listed as 0
+    shape_info(c->ndim, idx == 0 && ct_of(c) == CT_TRANSFER ? kernel_shape(c) : idx, tx, ty, tz, block);
     return BUB_OK;
 }
 

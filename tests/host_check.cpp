@@ -215,6 +215,27 @@ static void shapes()
         }
 }
 
+// The shape that transfer contents report is the one that their stages run.
+static void contents()
+{
+    for (int ndim = 1; ndim <= 3; ++ndim) {
+        Problem p = ndim == 1 ? Problem(1, 400, 1, 1, 11) : ndim == 2 ? Problem(2, 70, 37, 1, 11) : Problem(3, 20, 13, 11, 3);
+        bub_ctx *c = p.transfer().make();
+        int i = -1, t[4];
+        CHECK(bub_tile_get(c, &i) == BUB_OK && i == 0, "shape %d", i);
+        CHECK(bub_tile_info(c, i, &t[0], &t[1], &t[2], &t[3]) == BUB_OK, "info");
+        CHECK(bub_tile_set(c, 0) == BUB_OK && bub_tile_set(c, 1) == BUB_EUNSUPPORTED, "set");
+        bub_bin_groups(c, 1);
+        CHECK(bub_rhs_stage(c, pretend(1), pretend(2), nullptr) == BUB_OK, "rhs");
+        const FakeLaunch &l = fake().launches.back();
+        unsigned tiles = 1;
+        for (int d = 0; d < 3; ++d) tiles *= (p.grid.n[d] + t[d] - 1) / t[d];
+        CHECK(l.block.x == (unsigned)t[3] && l.grid.x == 8 * ((tiles + 7) / 8), "%dD: %u workgroups of %u threads; %d x %d x %d by %d listed",
+              ndim, l.grid.x, l.block.x, t[0], t[1], t[2], t[3]);
+        bub_ctx_destroy(c);
+    }
+}
+
 int main(int argc, char **argv)
 {
     const std::string name = argc > 1 ? argv[1] : "";
@@ -223,6 +244,7 @@ int main(int argc, char **argv)
     else if (name == "unused") unused();
     else if (name == "cache") cache();
     else if (name == "shapes") shapes();
+    else if (name == "contents") contents();
     else if (name == "classes") classes();
     else return 2;
     std::printf("%d failures\n", failures);
