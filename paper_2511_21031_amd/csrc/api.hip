@@ -117,6 +117,7 @@ template <> struct Tile<3, 3> { static constexpr int TX = 8, TY = 8, TZ = 3, BLO
 template <> struct Tile<3, 4> { static constexpr int TX = 8, TY = 8, TZ = 7, BLOCK = 512; };
 constexpr int TILE_COUNT[4] = {0, 4, 6, 5};
 constexpr int LINE_SHAPE = 3;   // the last 1D shape: one wave per tile of 63 cells (line_kernel.hpp)
+static_assert(GROUP_TILES[1] == LINE_SHAPE && GROUP_TILES[2] == TILE_COUNT[2] && GROUP_TILES[3] == TILE_COUNT[3], "grouped shapes");
 
 template <int D, int V>
 void tile_info(int *tx, int *ty, int *tz, int *block)
@@ -1966,7 +1967,7 @@ int bub_rhs_stage_noalloc(const bub_grid *grid, const bub_liquid *liq, const bub
 // ---------------------------------------------------------------------------
 namespace {
 
-// The member's view for the grouped kernels; the stage decomposition is the one its own launch uses.
+// The member's view for the grouped kernels; the stage decomposition is that of the shape its grouped kernel has.
 int member_desc(const bub_batch::Member &m, BatchMember *d)
 {
     const bub_ctx *c = m.ctx;
@@ -1986,7 +1987,7 @@ int member_desc(const bub_batch::Member &m, BatchMember *d)
     d->max_substeps = c->opts.max_substeps > 0 ? c->opts.max_substeps : 10000;
     d->sources = c->opts.bubble_mode == BUB_BUBBLES_UNSPLIT;
     int tx, ty, tz, blk;
-    shape_info(c->ndim, shape_of(c), &tx, &ty, &tz, &blk);
+    shape_info(c->ndim, group_tile(c->ndim, shape_of(c)), &tx, &ty, &tz, &blk);
     d->ntile[0] = (c->g.n[0] + tx - 1) / tx;
     d->ntile[1] = (c->g.n[1] + ty - 1) / ty;
     d->ntile[2] = (c->g.n[2] + tz - 1) / tz;
@@ -2015,7 +2016,7 @@ int batch_rebuild(bub_batch *b, hipStream_t s)
         if (rc) return rc;
         const bub_ctx *c = m.ctx;
         const int S = slots_for(c->N, c->nb);
-        pm.push_back({(int)i, c->ndim, S, shape_of(c), c->opts.bubble_mode == BUB_BUBBLES_SPLIT,
+        pm.push_back({(int)i, c->ndim, S, group_tile(c->ndim, shape_of(c)), c->opts.bubble_mode == BUB_BUBBLES_SPLIT,
                       (c->N + slot_cells(S) - 1) / slot_cells(S), (long long)tab[i].nitems});
     }
     BatchPlan plan;
@@ -2116,7 +2117,7 @@ void launch_stage_group_v(const bub_batch *b, const bub_batch::Launch &l, int st
     else launch_stage_group_t<D, V, double>(b, l, stage, s);
 }
 
-void stage_groups(const bub_batch *b, int stage, hipStream_t s)
+int stage_groups(const bub_batch *b, int stage, hipStream_t s)
 {
     for (const auto &l : b->stage_l) {
         const int v = l.key;
@@ -2124,7 +2125,8 @@ void stage_groups(const bub_batch *b, int stage, hipStream_t s)
         case 1:
             if (v == 1) launch_stage_group_v<1, 1>(b, l, stage, s);
             else if (v == 2) launch_stage_group_v<1, 2>(b, l, stage, s);
-            else launch_stage_group_v<1, 0>(b, l, stage, s);
+            else if (v == 0) launch_stage_group_v<1, 0>(b, l, stage, s);
+            else return BUB_EUNSUPPORTED;
             break;
         case 2:
             if (v == 1) launch_stage_group_v<2, 1>(b, l, stage, s);
@@ -2132,17 +2134,20 @@ void stage_groups(const bub_batch *b, int stage, hipStream_t s)
             else if (v == 3) launch_stage_group_v<2, 3>(b, l, stage, s);
             else if (v == 4) launch_stage_group_v<2, 4>(b, l, stage, s);
             else if (v == 5) launch_stage_group_v<2, 5>(b, l, stage, s);
-            else launch_stage_group_v<2, 0>(b, l, stage, s);
+            else if (v == 0) launch_stage_group_v<2, 0>(b, l, stage, s);
+            else return BUB_EUNSUPPORTED;
             break;
         default:
             if (v == 1) launch_stage_group_v<3, 1>(b, l, stage, s);
             else if (v == 2) launch_stage_group_v<3, 2>(b, l, stage, s);
             else if (v == 3) launch_stage_group_v<3, 3>(b, l, stage, s);
             else if (v == 4) launch_stage_group_v<3, 4>(b, l, stage, s);
-            else launch_stage_group_v<3, 0>(b, l, stage, s);
+            else if (v == 0) launch_stage_group_v<3, 0>(b, l, stage, s);
+            else return BUB_EUNSUPPORTED;
             break;
         }
     }
+    return BUB_OK;
 }
 
 // nsteps CFL-limited SSP-RK3 steps of every listed member: the phases of bub_rk3_step, each one
@@ -2150,6 +2155,7 @@ void stage_groups(const bub_batch *b, int stage, hipStream_t s)
 int batch_chunk(const bub_batch *b, int nsteps, hipStream_t s)
 {
     const bool any_split = !b->prim_split.empty();
+    int rc;
     for (int k = 0; k < nsteps; ++k) {
         prim_groups(b, b->prim_all, 0, true, s);                      // primitives and wave speeds of u^n
         hipLaunchKernelGGL(k_dt_group, dim3((unsigned)b->dt_count), dim3(WMAX_SLOTS), 0, s, b->d_tab,
@@ -2158,11 +2164,11 @@ int batch_chunk(const bub_batch *b, int nsteps, hipStream_t s)
             bubble_groups(b, s);                                         // S_b(dt/2)
             prim_groups(b, b->prim_split, 0, false, s);
         }
-        stage_groups(b, 1, s);
+        if ((rc = stage_groups(b, 1, s))) return rc;
         prim_groups(b, b->prim_all, 1, false, s);
-        stage_groups(b, 2, s);
+        if ((rc = stage_groups(b, 2, s))) return rc;
         prim_groups(b, b->prim_all, 2, false, s);
-        stage_groups(b, 3, s);
+        if ((rc = stage_groups(b, 3, s))) return rc;
         if (any_split) bubble_groups(b, s);                              // S_b(dt/2)
     }
     return hipGetLastError() == hipSuccess ? BUB_OK : BUB_EHIP;

@@ -13,11 +13,16 @@
 
 namespace bub {
 
+// Stage shapes that have a grouped kernel, per dimensionality; a member of another shape (the wave tiles of 1D) takes
+// shape 0 in a grouped launch, which gives the same bits.
+constexpr int GROUP_TILES[4] = {0, 3, 6, 5};
+constexpr int group_tile(int ndim, int tile) { return tile >= 0 && tile < GROUP_TILES[ndim] ? tile : 0; }
+
 struct PlanMember {
     int slot;              // batch slot (index into the member table)
     int ndim;
     int slots_per_cell;    // threads per cell of the primitive pass and bubble half-step
-    int tile;              // stage tile shape index
+    int tile;              // stage tile shape index (group_tile of the member's)
     bool split;            // bubble half-steps (split mode)
     long long pblocks;     // primitive/bubble blocks
     long long nitems;      // stage work items (tiles x bin groups)
