@@ -132,8 +132,9 @@ typedef struct bub_ctx bub_ctx;
 /* Create a context for one problem on the current HIP device.  Computes the bin
  * table on the host and allocates the context's device buffers
  * (about (ndim+6)*N*8 bytes; twice that where its stages can carry the primitive
- * pass of the state they write: grids of 2^19 cells or more, 2D and 3D ones from
- * 2^14 on, and one-bin problems).  *out receives the context (caller destroys it). */
+ * pass of the state they write: grids of 2^19 cells or more, with polytropic air or
+ * transfer contents 2D and 3D ones from 2^14 on).  *out receives the context
+ * (caller destroys it). */
 int bub_ctx_create(const bub_grid *grid, const bub_liquid *liq, const bub_gas *gas,
                    const bub_bins *bins, const bub_opts *opts, bub_ctx **out);
 

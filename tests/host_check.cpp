@@ -236,6 +236,26 @@ static void contents()
     }
 }
 
+// Threads a cell of the primitive pass at the sizes that the GPU tests take for them.
+static void threads()
+{
+    const struct { Problem p; int threads; } all[] = {
+        {Problem(2, 700, 760, 1, 3), 1}, {Problem(2, 600, 500, 1, 5), 2}, {Problem(2, 150, 140, 1, 5), 4}, {Problem(2, 150, 150, 1, 7), 8},
+        {Problem(2, 211, 203, 1, 11), 8}, {Problem(2, 200, 190, 1, 11), 8}, {Problem(3, 32, 32, 30, 11), 8},
+        {Problem(2, 100, 100, 1, 17), 16}, {Problem(2, 45, 40, 1, 31), 32}, {Problem(1, 1800, 1, 1, 31), 32}, {Problem(2, 160, 150, 1, 1), 2},
+    };
+    for (auto &a : all) {
+        bub_ctx *c = a.p.make();
+        CHECK(bub_moments(c, pretend(1), pretend(2), nullptr) == BUB_OK, "moments");
+        const FakeLaunch &l = fake().launches.back();
+        const long long cells = (long long)a.p.grid.n[0] * a.p.grid.n[1] * a.p.grid.n[2];
+        const double per = (double)l.grid.x * l.block.x / cells;   // (the last workgroup may be partly idle)
+        CHECK(per >= a.threads && per < a.threads * 1.2, "%lld cells, %d bins: %g threads a cell, not %d", cells, a.p.bins.nb, per,
+              a.threads);
+        bub_ctx_destroy(c);
+    }
+}
+
 int main(int argc, char **argv)
 {
     const std::string name = argc > 1 ? argv[1] : "";
@@ -245,6 +265,7 @@ int main(int argc, char **argv)
     else if (name == "cache") cache();
     else if (name == "shapes") shapes();
     else if (name == "contents") contents();
+    else if (name == "threads") threads();
     else if (name == "classes") classes();
     else return 2;
     std::printf("%d failures\n", failures);

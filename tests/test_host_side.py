@@ -24,7 +24,7 @@ def host_check(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("name", ["budget", "scratch", "unused", "cache", "classes", "shapes", "contents"])
+@pytest.mark.parametrize("name", ["budget", "scratch", "unused", "cache", "classes", "shapes", "contents", "threads"])
 def test_host_side(host_check, name, tmp_path):
     res = subprocess.run([host_check, name], capture_output=True, text=True, cwd=tmp_path)
     assert res.returncode == 0, res.stdout + res.stderr
