@@ -97,7 +97,7 @@ int blocks_for(long long n, int per = 256)
 }
 
 // Tile shapes of the stage kernel per dimensionality: (TX, TY, TZ, BLOCK).
-// Shape 0 is the default; the autotuner may pick another per context.
+// shape_of has a context's default; the autotuner may pick another.
 template <int D, int V> struct Tile;
 template <> struct Tile<1, 0> { static constexpr int TX = 255, TY = 1, TZ = 1, BLOCK = 256; };
 template <> struct Tile<1, 1> { static constexpr int TX = 127, TY = 1, TZ = 1, BLOCK = 128; };

@@ -101,7 +101,7 @@ __global__ void __launch_bounds__(S * CELLS) k_bubble_group(const BatchMember *_
 template <int D, int TX_, int TY_, int TZ_, int BLOCK, typename TF>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((D <= 2 && sizeof(TF) == 4) ? 5 : 1))) k_stage_group(const BatchMember *__restrict__ tab, const LaunchList *__restrict__ L, int stage, int nblk_per_xcd)
 {
-    BUB_STAGE_SHARED(D, TX_, TY_, TZ_, BLOCK, TF, 2)
+    BUB_STAGE_SHARED(D, TX_, TY_, TZ_, BLOCK, TF)
     const int b = blockIdx.x;
     const int item = (b & 7) * nblk_per_xcd + (b >> 3);
     if (item >= L->start[L->count]) return;

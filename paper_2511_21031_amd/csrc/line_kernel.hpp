@@ -34,11 +34,6 @@ __device__ __forceinline__ float next_lane(float x)
     return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), 0x130, 0xf, 0xf, true));
 }
 
-template <typename TF>
-struct alignas(2 * sizeof(TF)) Pair {
-    TF a, b;
-};
-
 // A launch of the kernel: RK stage, RK stage with the primitive pass of its result, right-hand side.
 enum LineMode : int { LM_RK = 0, LM_FUSE = 1, LM_RHS = 2 };
 

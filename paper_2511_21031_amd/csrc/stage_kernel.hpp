@@ -102,16 +102,22 @@ struct Geo {
     }
 };
 
-// LDS needs of one tile: coef[F] and scr[SCR] of TF, flag[F] bytes.  NF: state fields per bin (2, or 4
-// for transfer contents), each with a line array and a face array.
-template <int D, int TX_, int TY_, int TZ_, typename TF, int NF = 2>
+// LDS needs of one tile: coef[F] and scr[SCR] of TF, flag[F] bytes; a bin's R and Rdot have a line array and a face
+// array each.
+template <int D, int TX_, int TY_, int TZ_, typename TF>
 struct StageLds {
     using G = Geo<D, TX_, TY_, TZ_>;
     // line arrays of R and Rdot are LP apart, a multiple of 64 elements, so one paired LDS
     // access (64-element stride form) serves both
     static constexpr int LP = (G::L + 63) / 64 * 64;
-    static constexpr int SCR = (G::NCF * G::F > NF * LP + NF * G::F) ? G::NCF * G::F : NF * LP + NF * G::F;
+    static constexpr int SCR = (G::NCF * G::F > 2 * LP + 2 * G::F) ? G::NCF * G::F : 2 * LP + 2 * G::F;
     static constexpr int BYTES = (G::F + SCR) * (int)sizeof(TF) + G::F;
+};
+
+// Two bin variables of a cell or a face, staged and read as one.
+template <typename TF>
+struct alignas(2 * sizeof(TF)) Pair {
+    TF a, b;
 };
 
 // Mixture face between the cells f-1 and f of direction d: WENO5 of the primitives (ld(v, o): primitive v of
@@ -373,9 +379,8 @@ __device__ __forceinline__ void stage_tile(const StageArgs &A, const Grid &g, co
     const bool own_un = active && !A.rhs_mode && A.a != 0.0;
     double pre_nr = own_un ? A.qn[(long long)(iNR + b0) * N + gc] : 0.0;
     double pre_nv = own_un ? A.qn[(long long)(iNV + b0) * N + gc] : 0.0;
-    constexpr int NF = 2;
-    constexpr int LP = StageLds<D, TX_, TY_, TZ_, TF, NF>::LP;
-    TF *s_R = s_scr, *s_V = s_scr + LP, *s_fR = s_scr + NF * LP, *s_fV = s_scr + NF * LP + F;
+    constexpr int LP = StageLds<D, TX_, TY_, TZ_, TF>::LP;
+    TF *s_R = s_scr, *s_V = s_scr + LP, *s_fR = s_scr + 2 * LP, *s_fV = s_scr + 2 * LP + F;
     // In 3D the owned cell's two results of a bin wait in this thread's own s_out slots and go
     // to HBM one bin late, ahead of the next bin's loads, so that the wait for those loads at
     // the next staging does not also wait for stores issued just before it (measured: 1-3 %
@@ -441,7 +446,6 @@ __device__ __forceinline__ void stage_tile(const StageArgs &A, const Grid &g, co
                     vv[o] = s_V[st + o * sd];
                 }
                 TF RK, VK;
-                [[maybe_unused]] TF pp[5], mm[5];
                 if (fl & 2) {
                     RK = rr[2];
                     VK = vv[2];
@@ -521,9 +525,9 @@ __device__ __forceinline__ void stage_tile(const StageArgs &A, const Grid &g, co
 }
 
 // The LDS arrays of one stage workgroup, declared in the kernel that uses them.
-#define BUB_STAGE_SHARED(D, TX_, TY_, TZ_, BLOCK, TF, NF)                               \
+#define BUB_STAGE_SHARED(D, TX_, TY_, TZ_, BLOCK, TF)                                   \
     __shared__ TF s_coef[Geo<D, TX_, TY_, TZ_>::F];                                       \
-    __shared__ TF s_scr[StageLds<D, TX_, TY_, TZ_, TF, NF>::SCR];                         \
+    __shared__ TF s_scr[StageLds<D, TX_, TY_, TZ_, TF>::SCR];                             \
     __shared__ unsigned char s_flag[Geo<D, TX_, TY_, TZ_>::F];                            \
     __shared__ double s_out[D == 3 ? 2 * BLOCK : 1]; /* 3D: results stored one bin late */ \
     __shared__ double s_pp[PPOW_N];                  /* constants of the polytropic power */ \
@@ -559,7 +563,7 @@ __host__ __device__ constexpr int stage_waves()
 template <int D, int TX_, int TY_, int TZ_, int BLOCK, typename TF, bool FUSE, int CT>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(stage_waves<D, BLOCK, TF, FUSE, CT>()))) k_stage(StageArgs A, Grid g, Phys ph, Bins bins)
 {
-    BUB_STAGE_SHARED(D, TX_, TY_, TZ_, BLOCK, TF, 2)
+    BUB_STAGE_SHARED(D, TX_, TY_, TZ_, BLOCK, TF)
     // XCD-aware order: consecutive items land on the same XCD (blocks are dealt round-robin), and
     // the bin groups of a tile are consecutive items, so they share that XCD's L2.
     const int b = blockIdx.x;

@@ -17,11 +17,6 @@
 
 namespace bub {
 
-template <typename TF>
-struct alignas(2 * sizeof(TF)) TPair {
-    TF a, b;
-};
-
 enum TileMode : int { TM_RK = 0, TM_FUSE = 1, TM_RHS = 2 };
 
 // 2D: cells and halos of a tile in one plane of rows (corners unused); 3D: a line array per direction.
@@ -50,7 +45,7 @@ __global__ void __launch_bounds__(BLOCK) k_tile(StageArgs A, Grid g, Phys ph, Bi
 {
     using G = Geo<D, TX, TY, TZ>;
     using S = TileLds<D, TX, TY, TZ>;
-    using PT = TPair<TF>;
+    using PT = Pair<TF>;
     static_assert(G::FX <= BLOCK && G::FY <= BLOCK && G::FZ <= BLOCK && G::T <= BLOCK, "balanced tiles");
     constexpr bool TR = CT == CT_TRANSFER, FUSE = MODE == TM_FUSE, RHS = MODE == TM_RHS;
     constexpr int T = G::T, C = G::C, NCF = G::NCF, NP = TR ? 2 : 1, NF = 2 * NP;
