@@ -27,7 +27,7 @@ inline double group_cost(long long nw, int waves, int bins, bool light)
 // 150 x 80 x 31 with 16, 4, 3 groups 152, 135, 145.  In 1D a mixture face has one direction and a tile few halo cells,
 // so a repeat costs less, and the nearest number to 1024 workgroups of four wavefronts is best (kappa = 5/3 FP64:
 // 60000 x 31 with 2, 4, 5 groups 149, 138, 137 us, 100000 x 31 with 1, 3 237, 188, 250000 x 11 with 1, 2 193, 211;
-// 1 % behind the best number on average, 11 % at worst, where group_cost is 8 and 53 %).
+// 1 % behind the best number on average, 11 % at worst, where group_cost is 6 and 53 %).
 // forced: the caller's number (0: by this rule).
 // Returns the bins per group; *groups receives the workgroups per tile.
 inline int bins_per_group(int ndim, long long ntiles, int waves, int nb, bool light, int forced, int *groups)
