@@ -25,8 +25,8 @@
  *    density and R, Rdot the radius and wall velocity of each equilibrium-radius
  *    bin.  n is not stored: alpha = (4 pi/3) n mean(R^3) (eq. e:ndf) gives
  *    n = sqrt((4 pi/3) sum_i w_i (nR_i)^3 / alpha).
- *  * A context owns only its own small device buffers (bin table, one
- *    primitive scratch field set, scalars for the time step and the error
+ *  * A context owns only its own small device buffers (bin table, one or two
+ *    primitive scratch field sets, scalars for the time step and the error
  *    word) and is not thread-safe: calls on one context must be serialised by
  *    the caller (one stream per context is the intended use).
  *  * Numerical failures found on the device (non-finite state, non-positive
@@ -240,9 +240,11 @@ int bub_get_time(bub_ctx *ctx, double *t);
 
 /* nsteps calls of bub_rk3_step in one (same arguments; dt_dev receives the last
  * step's dt).  Results are bitwise those of nsteps separate calls.  In unsplit
- * mode on grids of 2^19 cells or more, the last stage of each step but the
- * final one also computes the primitives and wave speeds of the state it
- * writes, so later steps start without a primitive pass of their own.
+ * mode, where stages carry the primitive pass (a context with a second scratch,
+ * on grids where that pays), the last stage of each step but the final one also
+ * computes the primitives and wave speeds of the state it writes, in split mode
+ * the closing half-step does (but for the general polytropic power), so later
+ * steps start without a primitive pass of their own.
  * BUB_EINVAL for nsteps < 0 or the argument errors of bub_rk3_step. */
 int bub_rk3_steps(bub_ctx *ctx, double *q, double *work, int nsteps, double dt, double *dt_dev, void *stream);
 
