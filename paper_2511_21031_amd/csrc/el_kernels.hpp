@@ -111,15 +111,16 @@ __device__ inline void el_support(const double *b, long long nb, long long i, co
 // Visit the cells of a bubble's kernel support (eq. kernel3D: cut off at distance 3h).  The lanes of the
 // bubble's wavefront take the (x, y) points of the (2m+1)^2 stencil plane (more passes when it exceeds 64)
 // and each walks the 2m+1 z planes of its column, so no lane divides by the stencil width per cell.
-// f(c, e, ld(c)) for every cell c inside the domain and the cut-off, e = exp(-d^2 / (2 h^2)) (the Gaussian
+// f(c, e) for every cell c inside the domain and the cut-off, e = exp(-d^2 / (2 h^2)) (the Gaussian
 // without its normalisation), as the column's factor times the plane's: one exponential per column and, on
 // the plane's own lane, one per plane (handed round by readlane, 64 planes at a time) in place of one per cell:
 // the gather of 1e5 bubbles 0.130 -> 0.118 ms.  Every lane stays in the loops, as a lane that has left one no longer
-// holds its plane's factor for the others; ld and f alone are conditional.  U: planes whose ld are in flight together
-// (wide supports, one load's latency after the other: the gather of 100 bubbles of 11 dx 1.69 ms with one, 1.30 with two).
-template <int U, typename LD, typename F>
+// holds its plane's factor for the others; f alone is conditional.  (Two planes' loads in flight for supports 17 cells
+// and wider took 100 bubbles of 11 dx from 1.69 to 1.29 ms, but as a second loop in the gather the 1e5 bubbles of 7 cells
+// from 0.139 to 0.143.)
+template <typename F>
 __device__ __forceinline__ void el_visit(const ElGrid &g, const int host[3], const double xb[3], double h, int m,
-                                         int lane, LD &&ld, F &&f)
+                                         int lane, F &&f)
 {
     const int w = __builtin_amdgcn_readfirstlane(2 * m + 1), w2 = w * w;
     const double cut = 9.0 * h * h, nh = -0.5 / (h * h);
@@ -142,39 +143,13 @@ __device__ __forceinline__ void el_visit(const ElGrid &g, const int host[3], con
         for (int z0 = 0; z0 < w; z0 += 64) {
             if (w > 64) zf = plane(z0);
             const int zlo = __double2loint(zf), zhi = __double2hiint(zf), nz = w - z0 < 64 ? w - z0 : 64;
-            auto factor = [&](int k) {   // plane z0 + k's, held by lane k
-                return __hiloint2double(__builtin_amdgcn_readlane(zhi, k), __builtin_amdgcn_readlane(zlo, k));
-            };
-            if constexpr (U == 1) {
-                for (int k = 0; k < nz; ++k) {
-                    const int iz = host[2] - m + z0 + k;
-                    const int cz = el_wrap(iz, g.n[2], g.bc[2]);
-                    const double ez = (iz + 0.5) * g.dx - xb[2];
-                    const double d2 = dxy + ez * ez;
-                    const double e = exy * factor(k);
-                    if (in && cz >= 0 && d2 < cut) f(cxy + nxy * cz, e, ld(cxy + nxy * cz));
-                }
-            } else {
-                for (int k = 0; k < nz; k += U) {
-                    double v[U];
-                    long long c[U];
-                    bool on[U];
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const int iz = host[2] - m + z0 + k + u;
-                        const int cz = el_wrap(iz, g.n[2], g.bc[2]);
-                        const double ez = (iz + 0.5) * g.dx - xb[2];
-                        on[u] = in && k + u < nz && cz >= 0 && dxy + ez * ez < cut;
-                        c[u] = cxy + nxy * cz;
-                        v[u] = 0.0;
-                        if (on[u]) v[u] = ld(c[u]);
-                    }
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const double e = exy * factor((k + u) & 63);
-                        if (on[u]) f(c[u], e, v[u]);
-                    }
-                }
+            for (int k = 0; k < nz; ++k) {
+                const int iz = host[2] - m + z0 + k;
+                const int cz = el_wrap(iz, g.n[2], g.bc[2]);
+                const double ez = (iz + 0.5) * g.dx - xb[2];
+                const double d2 = dxy + ez * ez;
+                const double e = exy * __hiloint2double(__builtin_amdgcn_readlane(zhi, k), __builtin_amdgcn_readlane(zlo, k));
+                if (in && cz >= 0 && d2 < cut) f(cxy + nxy * cz, e);
             }
         }
     }
@@ -193,13 +168,10 @@ __global__ void __launch_bounds__(256) k_el_gather(const double *__restrict__ P,
     const double xb[3] = {b[BX_ * nb + i], b[BY_ * nb + i], b[BZ_ * nb + i]};
     // normalised weights: the Gaussian's constant factor cancels
     double sw = 0.0, swp = 0.0;
-    const auto ld = [&](long long c) { return P[4 * N + c]; };
-    const auto add = [&](long long, double e, double p) {
+    el_visit(g, host, xb, h, m, lane, [&](long long c, double e) {
         sw += e;
-        swp += e * p;
-    };
-    if (m >= 8) el_visit<2>(g, host, xb, h, m, lane, ld, add);   // (narrow ones have wavefronts enough: 0.141 ms with one, 0.149 with two)
-    else el_visit<1>(g, host, xb, h, m, lane, ld, add);
+        swp += e * P[4 * N + c];
+    });
     for (int s = 32; s > 0; s >>= 1) {
         sw += __shfl_xor(sw, s, 64);
         swp += __shfl_xor(swp, s, 64);
@@ -325,7 +297,7 @@ __global__ void __launch_bounds__(256) k_el_scatter(const double *__restrict__ b
     const double R = b[BRR * nb + i], V = b[BRD * nb + i];
     const double norm = 0.063493635934240969 / (h * h * h);   // (2 pi)^(-3/2) / h^3
     const double vol = FOUR_PI_3 * R * R * R * norm, rate = 3.0 * FOUR_PI_3 * R * R * V * norm;
-    el_visit<1>(g, host, xb, h, m, lane, [](long long) { return 0.0; }, [&](long long c, double e, double) {
+    el_visit(g, host, xb, h, m, lane, [&](long long c, double e) {
         atomicAdd(&aD[c], vol * e);
         atomicAdd(&aD[N + c], rate * e);
     });
